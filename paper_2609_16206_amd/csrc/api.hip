@@ -46,6 +46,7 @@ bool finite_nonneg(float x) { return std::isfinite(x) && x >= 0.0f; }
 constexpr int64_t kMaxNs = int64_t(1) << 40;
 constexpr int32_t kMaxBatchCap = 65536;
 constexpr int32_t kDefaultBatchCap = 256;
+constexpr int kSmallPool = 8;     // see plan_launch
 constexpr int kSimds = 256 * 4;  // MI355X: 256 compute units x 4 SIMDs
 
 // Limits of rt_sim_run_replicas_noalloc: the device scratch each GPU holds
@@ -146,6 +147,8 @@ bool class_fits(const rt::SimClass& c, const rt_point& p) {
   if ((c.kind == rt::kBat) != (p.service == RT_SERVICE_BATCHED)) return false;
   if (c.kind == rt::kBat)
     return c.MP == 0 || (p.n_prefill + c.MP - 1) / c.MP + (p.n_decode + c.MP - 1) / c.MP <= c.S;
+  if (c.kind == rt::kLseg)
+    return c.mode == point_mode(p) && (std::max(p.n_prefill, p.n_decode) + c.MP - 1) / c.MP <= c.S / 2;
   if (c.kind == rt::kSeg) {
     if (c.mode != point_mode(p)) return false;
     const int lanes = (p.n_prefill + c.MP - 1) / c.MP + (p.n_decode + c.MD - 1) / c.MD;
@@ -188,6 +191,7 @@ namespace {
 // kernel classes that hold each.
 struct rt_sim_points {
   size_t n;
+  const rt_point* points;
   const std::vector<int>* classes;
 };
 
@@ -220,32 +224,59 @@ struct PlanBufs {
   int* wider;        // [npts] working copy for the widening pass
   int64_t* count;    // [ncls] replicas per class
   int64_t* start;    // [ncls] first work-list slot per class
+  int32_t* max_inst;  // [ncls] largest P + D among a class's points
   double* cost;      // [ncls] request-lanes per class (launch order)
   int32_t* work;     // [n] replica ids, grouped by class
   int* act;          // [ncls] classes with work, dearest first
   int n_act;
 };
 
-// Plan.  Each point runs one kernel class.  With few replicas (fewer waves,
-// at the shortest-step classes, than twice the GPU's SIMDs) every replica is
-// a latency chain and takes the shortest-step class; with many, the GPU's
-// issue rate is the limit and each point takes the segment class with the
-// fewest issue slots per replica-step (lanes x step cost).  Then replicas
-// are grouped by class, longest first so that long chains start early (equal
-// lengths in replica order); empty replicas need no work.  Classes with work
-// are listed dearest first.  Allocates nothing.
+// Plan.  Each point runs one kernel class.
+//
+// Pools of at most kSmallPool instances a side always take the class with the
+// FIFOs in LDS (kLseg).  For the others the launch's size decides, counted in
+// waves of segments just wide enough for one instance per lane: with fewer than two
+// per SIMD every replica is a latency chain and takes the class with the
+// shortest step (kLseg while its waves are that few too: its halves make it up
+// to twice as wide); with more, the GPU's issue rate is the limit and each point
+// takes the segment class with the fewest issue slots per replica-step (lanes x
+// step cost).  Measured, ns per request of many replicas, ledger backlog: 2 + 3
+// instances kLseg 0.073, the best of kSeg 0.135; 2 + 6 0.097 and 0.102; 2 + 8
+// 0.099 and 0.111; 2 + 16 0.172 and 0.122; 2 + 32 0.31 and 0.21.
+//
+// Then replicas are grouped by class, longest first so that long chains start
+// early (equal lengths in replica order); empty replicas need no work.  Classes
+// with work are listed dearest first.  Allocates nothing.
 void plan_launch(const rt_sim_points& sp, int64_t n, PlanBufs& b) {
   const int ncls = rt::sim_class_count();
   const size_t npts = sp.n;
   for (size_t k = 0; k < npts; ++k) b.reps_of[k] = 0;
   for (int64_t i = 0; i < n; ++i)
     if (b.off[i + 1] > b.off[i]) b.reps_of[b.pp[i]] += 1;
-  double waves = 0.0;
-  for (size_t k = 0; k < npts; ++k) waves += (double)b.reps_of[k] * rt::sim_class(sp.classes[k][0]).S / 64.0;
-  const bool many = waves >= 2.0 * kSimds;
+  // (fitting classes are listed kLseg first, then in order of step length)
+  auto other = [&](size_t k) {  // a point's first class that is not kLseg
+    const std::vector<int>& fit = sp.classes[k];
+    size_t j = 0;
+    while (rt::sim_class(fit[j]).kind == rt::kLseg) ++j;
+    return fit[j];
+  };
+  double waves = 0.0, lds_waves = 0.0;
+  for (size_t k = 0; k < npts; ++k) {
+    const int inst = sp.points[k].n_prefill + sp.points[k].n_decode;
+    int S = rt::sim_class(other(k)).S;
+    while (rt::sim_class(other(k)).kind == rt::kSeg && S / 2 >= inst) S /= 2;
+    waves += (double)b.reps_of[k] * S / 64.0;
+    lds_waves += (double)b.reps_of[k] * rt::sim_class(sp.classes[k][0]).S / 64.0;
+  }
+  const bool many = waves >= 2.0 * kSimds, lds_many = many || lds_waves >= 2.0 * kSimds;
   for (size_t k = 0; k < npts; ++k) {
     const std::vector<int>& fit = sp.classes[k];
-    b.choice[k] = fit[0];
+    const bool small = std::max(sp.points[k].n_prefill, sp.points[k].n_decode) <= kSmallPool;
+    if (rt::sim_class(fit[0]).kind == rt::kLseg && (small || !lds_many)) {
+      b.choice[k] = fit[0];
+      continue;
+    }
+    b.choice[k] = other(k);
     if (!many) continue;
     double best = -1.0;
     for (int c : fit) {
@@ -271,7 +302,7 @@ void plan_launch(const rt_sim_points& sp, int64_t n, PlanBufs& b) {
         if (b.reps_of[k] == 0) continue;
         const rt::SimClass sc = rt::sim_class(b.choice[k]);
         w1 += std::ceil((double)b.reps_of[k] * sc.S / 64.0);
-        if ((sc.kind == rt::kSeg || sc.kind == rt::kBat) && sc.MP == 1 && sc.S < 64)
+        if (sc.kind != rt::kWseg && sc.MP == 1 && sc.S < 64)
           for (int c : sp.classes[k]) {
             const rt::SimClass wc = rt::sim_class(c);
             if (wc.kind == sc.kind && wc.mode == sc.mode && wc.MP == 1 && wc.S == 2 * sc.S) b.wider[k] = c;
@@ -286,6 +317,10 @@ void plan_launch(const rt_sim_points& sp, int64_t n, PlanBufs& b) {
   for (int c = 0; c < ncls; ++c) b.count[c] = 0;
   for (int64_t i = 0; i < n; ++i)
     if (b.off[i + 1] > b.off[i]) b.count[b.choice[b.pp[i]]] += 1;
+  for (int c = 0; c < ncls; ++c) b.max_inst[c] = 0;
+  for (size_t k = 0; k < npts; ++k)
+    if (b.reps_of[k] > 0)
+      b.max_inst[b.choice[k]] = std::max(b.max_inst[b.choice[k]], sp.points[k].n_prefill + sp.points[k].n_decode);
   int64_t pos = 0;
   for (int c = 0; c < ncls; ++c) {
     b.start[c] = pos;
@@ -535,6 +570,7 @@ static rt::SimArgs sim_args(const rt_sim* sim, const rt_trace* trace, const rt_s
   a.span = out->decode_span_ns;
   a.work = nullptr;
   a.n_work = 0;
+  a.max_inst = 0;
   // record planes by record size: index 0 of each pool's plane
   for (int k = 0; k < 2; ++k) planes[0][k] = planes[1][k] = nullptr;
   for (int k = 0; k < 2 && sc && L.any_serial; ++k) {
@@ -553,6 +589,7 @@ static hipError_t launch_class(int c, rt::SimArgs a, const PlanBufs& b, const in
                                const rt::BatScratch* bs, hipStream_t where) {
   a.work = d_work + b.start[c];
   a.n_work = b.count[c];
+  a.max_inst = b.max_inst[c];
   const int lg = rt::mode_ledger(rt::sim_class(c).mode) ? 1 : 0;
   a.rec[0] = planes[lg][0];
   a.rec[1] = planes[lg][1];
@@ -587,11 +624,12 @@ rt_status rt_sim_run_replicas(rt_sim* sim, const rt_trace* trace, rt_sim_out* ou
   const size_t npts = sim->points.size();
   std::vector<int64_t> reps_of(npts), count(ncls), start(ncls);
   std::vector<int> choice(npts), wider(npts), act(ncls);
+  std::vector<int32_t> max_inst(ncls);
   std::vector<double> cost(ncls);
   std::vector<int32_t> work_list(n);
   PlanBufs b{off.data(), pp.data(), reps_of.data(), choice.data(), wider.data(), count.data(), start.data(),
-             cost.data(), work_list.data(), act.data(), 0};
-  plan_launch(rt_sim_points{npts, sim->point_classes.data()}, n, b);
+             max_inst.data(), cost.data(), work_list.data(), act.data(), 0};
+  plan_launch(rt_sim_points{npts, sim->points.data(), sim->point_classes.data()}, n, b);
   if ((st = check_sample_bits(sim, trace, b, "rt_sim_run_replicas")) != RT_OK) return st;
 
   hipError_t e;
@@ -730,6 +768,7 @@ struct NoAllocHost {
   int64_t reps_of[kNoAllocMaxPoints];
   int choice[kNoAllocMaxPoints], wider[kNoAllocMaxPoints];
   int64_t count[kMaxClassSlots], start[kMaxClassSlots];
+  int32_t max_inst[kMaxClassSlots];
   double cost[kMaxClassSlots];
   int act[kMaxClassSlots];
 };
@@ -764,8 +803,8 @@ rt_status rt_sim_run_replicas_noalloc(rt_sim* sim, const rt_trace* trace, rt_sim
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return hip_fail(e, "reading offsets/param_point");
   if ((st = check_plan_inputs(sim, trace, h.off, h.pp, fn)) != RT_OK) return st;
-  PlanBufs b{h.off, h.pp, h.reps_of, h.choice, h.wider, h.count, h.start, h.cost, h.work, h.act, 0};
-  plan_launch(rt_sim_points{sim->points.size(), sim->point_classes.data()}, n, b);
+  PlanBufs b{h.off, h.pp, h.reps_of, h.choice, h.wider, h.count, h.start, h.max_inst, h.cost, h.work, h.act, 0};
+  plan_launch(rt_sim_points{sim->points.size(), sim->points.data(), sim->point_classes.data()}, n, b);
   if ((st = check_sample_bits(sim, trace, b, fn)) != RT_OK) return st;
   for (int k = 0; k < b.n_act; ++k)
     if (rt::sim_class(b.act[k]).kind == rt::kBat)

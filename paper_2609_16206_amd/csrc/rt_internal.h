@@ -40,6 +40,7 @@ struct SimArgs {
   const DevPoint* points;
   const int32_t* work;  // replica ids of this launch, in processing order
   int64_t n_work;
+  int32_t max_inst;  // largest P + D among the launch's points (classes with the FIFOs in LDS)
   const int64_t* offsets;
   const int32_t* param_point;  // may be null: every replica uses point 0
   const int64_t* arrival;
@@ -79,8 +80,10 @@ constexpr int kDummyRecords = 1024;  // a power of two
 // backlog, ledger backlog, or a baseline policy; the two learned ones also
 // over two sampled candidates per pool).  kWseg: the same for one replica
 // per workgroup of S / 64 waves, instances dealt round-robin over the waves.
+// kLseg: one replica per aligned segment of S <= 64 lanes of one wave, a pool
+// on each half, one instance per lane, FIFOs in LDS.
 // kBat: the continuous-batching service model, one replica per lane.
-enum SimKind { kSeg = 0, kWseg = 1, kBat = 2 };
+enum SimKind { kSeg = 0, kWseg = 1, kBat = 2, kLseg = 3 };
 enum SimMode { kModeTrue = 0, kModeProxy = 1, kModeBase = 2, kModeTrueSampled = 3, kModeProxySampled = 4 };
 constexpr bool mode_ledger(int m) { return m == kModeProxy || m == kModeProxySampled; }  // proxy backlog
 constexpr bool mode_sampled(int m) { return m == kModeTrueSampled || m == kModeProxySampled; }

@@ -1,4 +1,5 @@
 // The segment-kernel classes: every (S, M) compiled, for each scoring mode.
+#include "lseg_kernel.h"
 #include "seg_kernel.h"
 #include "wseg_kernel.h"
 
@@ -17,6 +18,11 @@ struct SegShape {
 const SegShape kShapes[] = {RT_SEG_FOR_EACH(RT_SEG_SHAPE)};
 #undef RT_SEG_SHAPE
 constexpr int kNumShapes = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
+// One-wave segments with the FIFOs in LDS: lanes, one instance on each.
+#define RT_LSEG_SHAPE(S_) {S_, 1},
+const SegShape kLdsShapes[] = {RT_LSEG_FOR_EACH(RT_LSEG_SHAPE)};
+#undef RT_LSEG_SHAPE
+constexpr int kNumLds = (int)(sizeof(kLdsShapes) / sizeof(kLdsShapes[0]));
 // Multi-wave segments: {waves, instances per lane}, after the one-wave ones.
 #define RT_WSEG_SHAPE(W_, M_) {W_, M_},
 const SegShape kWideShapes[] = {RT_WSEG_FOR_EACH(RT_WSEG_SHAPE)};
@@ -37,9 +43,14 @@ constexpr int kNumBat = (int)(sizeof(kBatShapes) / sizeof(kBatShapes[0]));
 // The one-wave and multi-wave classes of every mode, then the batched
 // service model's classes (one replica per lane; their launch is
 // launch_bat).
-int sim_class_count() { return (kNumShapes + kNumWide) * kNumModes + kNumBat; }
+int sim_class_count() { return (kNumLds + kNumShapes + kNumWide) * kNumModes + kNumBat; }
 
 SimClass sim_class(int i) {
+  if (i < kNumLds * kNumModes) {
+    const SegShape& e = kLdsShapes[i % kNumLds];
+    return SimClass{kLseg, e.S, e.M, e.M, kModes[i / kNumLds]};
+  }
+  i -= kNumLds * kNumModes;
   if (i >= (kNumShapes + kNumWide) * kNumModes) {
     const SegShape& e = kBatShapes[i - (kNumShapes + kNumWide) * kNumModes];
     return SimClass{kBat, e.S, e.M, e.M, kModeTrue};
@@ -55,6 +66,14 @@ SimClass sim_class(int i) {
 
 hipError_t launch_sim(const SimClass& c, const SimArgs& a, hipStream_t stream) {
   if (c.kind == kBat) return hipErrorInvalidValue;  // needs its scratch: launch_bat
+  if (c.kind == kLseg) switch (c.mode) {
+      case kModeTrue: return seg::launch_lseg_mode<kModeTrue>(c.S, a, stream);
+      case kModeProxy: return seg::launch_lseg_mode<kModeProxy>(c.S, a, stream);
+      case kModeBase: return seg::launch_lseg_mode<kModeBase>(c.S, a, stream);
+      case kModeTrueSampled: return seg::launch_lseg_mode<kModeTrueSampled>(c.S, a, stream);
+      case kModeProxySampled: return seg::launch_lseg_mode<kModeProxySampled>(c.S, a, stream);
+      default: return hipErrorInvalidValue;
+    }
   const bool w = c.kind == kWseg;
   const int S = w ? c.S / 64 : c.S;
   switch (c.mode) {

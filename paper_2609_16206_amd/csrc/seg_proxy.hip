@@ -1,5 +1,6 @@
 // Segment-kernel and wide-segment-kernel instances for the proxy scoring
 // mode (one source file per mode, so that they compile in parallel).
+#include "lseg_kernel.h"
 #include "seg_kernel.h"
 #include "wseg_kernel.h"
 
@@ -21,6 +22,15 @@ hipError_t launch_mode<kModeProxy>(int S, int M, const SimArgs& a, hipStream_t s
 template <>
 hipError_t launch_wide_mode<kModeProxy>(int W, int M, const SimArgs& a, hipStream_t stream) {
   RT_WSEG_FOR_EACH(RT_WSEG_CASE)
+  return hipErrorInvalidValue;
+}
+
+#define RT_LSEG_CASE(S_) \
+  if (S == S_) return launch_lseg<S_, kModeProxy>(a, stream);
+
+template <>
+hipError_t launch_lseg_mode<kModeProxy>(int S, const SimArgs& a, hipStream_t stream) {
+  RT_LSEG_FOR_EACH(RT_LSEG_CASE)
   return hipErrorInvalidValue;
 }
 

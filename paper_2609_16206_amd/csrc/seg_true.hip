@@ -1,5 +1,6 @@
 // Segment-kernel and wide-segment-kernel instances for the true scoring
 // mode (one source file per mode, so that they compile in parallel).
+#include "lseg_kernel.h"
 #include "seg_kernel.h"
 #include "wseg_kernel.h"
 
@@ -21,6 +22,15 @@ hipError_t launch_mode<kModeTrue>(int S, int M, const SimArgs& a, hipStream_t st
 template <>
 hipError_t launch_wide_mode<kModeTrue>(int W, int M, const SimArgs& a, hipStream_t stream) {
   RT_WSEG_FOR_EACH(RT_WSEG_CASE)
+  return hipErrorInvalidValue;
+}
+
+#define RT_LSEG_CASE(S_) \
+  if (S == S_) return launch_lseg<S_, kModeTrue>(a, stream);
+
+template <>
+hipError_t launch_lseg_mode<kModeTrue>(int S, const SimArgs& a, hipStream_t stream) {
+  RT_LSEG_FOR_EACH(RT_LSEG_CASE)
   return hipErrorInvalidValue;
 }
 

@@ -1,5 +1,6 @@
 // Segment-kernel and wide-segment-kernel instances for the true scoring
 // mode over two sampled candidates per pool (one source file per mode).
+#include "lseg_kernel.h"
 #include "seg_kernel.h"
 #include "wseg_kernel.h"
 
@@ -21,6 +22,15 @@ hipError_t launch_mode<kModeTrueSampled>(int S, int M, const SimArgs& a, hipStre
 template <>
 hipError_t launch_wide_mode<kModeTrueSampled>(int W, int M, const SimArgs& a, hipStream_t stream) {
   RT_WSEG_FOR_EACH(RT_WSEG_CASE)
+  return hipErrorInvalidValue;
+}
+
+#define RT_LSEG_CASE(S_) \
+  if (S == S_) return launch_lseg<S_, kModeTrueSampled>(a, stream);
+
+template <>
+hipError_t launch_lseg_mode<kModeTrueSampled>(int S, const SimArgs& a, hipStream_t stream) {
+  RT_LSEG_FOR_EACH(RT_LSEG_CASE)
   return hipErrorInvalidValue;
 }
 

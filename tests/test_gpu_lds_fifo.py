@@ -1,0 +1,49 @@
+"""The one-wave kernel with its FIFOs in LDS (pools of at most 32 instances a
+side) where its ring can go wrong: queues far beyond the ring that then drain
+many requests between two arrivals (refills one step ahead and at once), the
+edges of the segment widths, every scoring mode, few replicas (large rings)
+and many (small ones)."""
+import numpy as np
+import pytest
+
+from paper_2609_16206_amd import workload as W
+from tests.gpu_common import log, run_sim
+from tests.parity import check_properties, follow_replicas, goodput_recount
+
+pytestmark = pytest.mark.gpu
+
+MODES = [("learned", "true"), ("learned", "proxy"), ("round_robin", "true"), ("least_loaded", "true"),
+         ("learned_sampled", "true"), ("learned_sampled", "proxy"), ("length_threshold", "true")]
+
+
+@pytest.mark.parametrize("n_rep,n_req", [(14, 3001), (3584, 130)])
+@pytest.mark.parametrize("P,D", [(1, 1), (4, 4), (5, 3), (8, 8), (2, 9), (16, 16), (17, 1), (32, 32)])
+def test_deep_rings_that_drain(P, D, n_rep, n_req):
+    pts = [W.make_point(P, D, n_classes=3, policy=pol, backlog_mode=bm, kv_cap=20_000, len_threshold=150)
+           for pol, bm in MODES]
+    traf = W.mixed_bursty()
+    # bursts of 60 to 700 requests at six times the capacity, then a lull that
+    # lets about two thirds of the queue finish before the next arrival
+    k = 6.0 * W.capacity_rps(pts[0], traf) / traf.mean_rate()
+    rng = np.random.default_rng(P * 64 + D)
+    lens = n_req - np.arange(n_rep) % 5
+    parts = []
+    for i in range(n_rep):
+        d = W.replica_arrays(43, i, traf.scaled(k), int(lens[i]))
+        gaps = np.diff(d["arrival_ns"], prepend=0)
+        at = np.cumsum(rng.integers(60, 700, 64))
+        at = at[at < lens[i]]
+        gaps[at] += (0.66 * np.diff(d["arrival_ns"][at], prepend=0) * 5.0).astype(np.int64)
+        d["arrival_ns"] = np.cumsum(gaps)
+        parts.append(d)
+    tr = {key: np.concatenate([q[key] for q in parts]) for key in parts[0]}
+    tr["offsets"] = np.concatenate(([0], np.cumsum(lens))).astype(np.int64)
+    tr["param_point"] = (np.arange(n_rep) % len(pts)).astype(np.int32)
+    W.add_sample_words(tr, 9)
+    gpu, g, met, flags = run_sim(pts, tr)
+    assert flags == 0
+    check_properties(pts, tr, gpu)
+    assert np.array_equal(goodput_recount(pts, tr, gpu), met)
+    reps = range(n_rep) if n_rep < 100 else range(0, n_rep, 31)
+    rep = follow_replicas(pts, tr, gpu, reps, gpu_goodput=g, gpu_met=met)
+    log(f"LDS FIFOs {P}+{D}, {n_rep} x {n_req}: {rep}")
