@@ -938,13 +938,14 @@ rt_status rt_score_argmin(const rt_router_params* prm, int32_t pool, int32_t n_i
     return fail(RT_EINVAL, "rt_score_argmin: null array");
   if (inst_stride != 0 && n_req > INT64_MAX / inst_stride) return fail(RT_ERANGE, "rt_score_argmin: size overflow");
   rt::ScoreArgs a;
-  a.w_b = prm->w_b;
-  a.w_s = prm->w_s;
-  a.w_q = prm->w_q;
-  a.rho = prm->rho;
-  a.tau = pool == RT_POOL_DECODE ? prm->tau_dec_s : prm->tau_pre_s;
+  // (+0.0f turns a -0.0f into +0.0f and changes nothing else: no cost is -0 then)
+  a.w_b = prm->w_b + 0.0f;
+  a.w_s = prm->w_s + 0.0f;
+  a.w_q = prm->w_q + 0.0f;
+  a.rho = prm->rho + 0.0f;
+  a.tau = (pool == RT_POOL_DECODE ? prm->tau_dec_s : prm->tau_pre_s) + 0.0f;
   a.inv_cap = 1.0f / (float)kv_cap;
-  for (int c = 0; c < RT_MAX_CLASSES; ++c) a.sigma[c] = prm->sigma[c];
+  for (int c = 0; c < RT_MAX_CLASSES; ++c) a.sigma[c] = prm->sigma[c] + 0.0f;
   a.pool = pool;
   a.n_inst = n_inst;
   a.stride = inst_stride;

@@ -101,6 +101,16 @@ __device__ __forceinline__ uint32_t cross_rows(uint32_t v, Op op) {
   return v;
 }
 
+// Minimum over the segment, on every lane of it.
+template <int S>
+__device__ __forceinline__ uint32_t seg_min(uint32_t v) {
+  if constexpr (S >= 2) v = min(v, dpp<0xB1>(v));
+  if constexpr (S >= 4) v = min(v, dpp<0x4E>(v));
+  if constexpr (S >= 8) v = min(v, dpp<0x141>(v));
+  if constexpr (S >= 16) v = min(v, dpp<0x140>(v));
+  return cross_rows<S>(v, [](uint32_t x, uint32_t y) { return min(x, y); });
+}
+
 // Two independent segment minima, interleaved so that each DPP step of one
 // fills the other's data-hazard wait.
 template <int S>

@@ -174,15 +174,6 @@ typedef __attribute__((address_space(3))) uint64_t lds_u64;
 // Does `c` hold on some lane (wave-uniform)?
 __device__ __forceinline__ bool any_lane(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
 
-template <int N>
-__device__ __forceinline__ uint32_t seg_min(uint32_t v) {
-  if constexpr (N >= 2) v = min(v, dpp<0xB1>(v));
-  if constexpr (N >= 4) v = min(v, dpp<0x4E>(v));
-  if constexpr (N >= 8) v = min(v, dpp<0x141>(v));
-  if constexpr (N >= 16) v = min(v, dpp<0x140>(v));
-  return cross_rows<N>(v, [](uint32_t x, uint32_t y) { return min(x, y); });
-}
-
 template <int S, int kMode>
 __global__ void __launch_bounds__(64 * kSegWaves) lseg_kernel(SimArgs a, LRings g) {
   constexpr bool kTok = mode_ledger(kMode);    // the ledger is priced

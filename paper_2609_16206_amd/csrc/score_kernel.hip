@@ -2,30 +2,31 @@
 // and the per-replica goodput reduction (Section IV-B SLO targets, Table II
 // goodput), for gfx950.
 //
-// Shared snapshot (inst_stride 0): the instance terms that do not depend on
-// the request, w_b * backlog and w_q * queue, are formed once per block into
-// LDS (the same float32 operations the equation performs first), then each
-// thread scores kReq requests against every instance, reading each LDS entry
-// once for all of its requests.  VALU-bound.
+// Shared snapshot (inst_stride 0), many requests: the instance terms that do
+// not depend on the request, w_b * backlog and w_q * queue, are formed once
+// per block into LDS (the same float32 operations the equation performs
+// first), then each thread scores kReq requests against every instance,
+// reading each LDS entry once for all of its requests.  VALU-bound.
 //
-// Per-request snapshot (inst_stride >= n_inst): rows of at most 64 instances
-// laid out for 16-byte loads take 16 lanes per request, four instances per
-// lane; any other shape takes a segment of S lanes per request that walks the
-// request's row with unit stride across lanes (coalesced), keeps a
-// lane-local best, and reduces (key, index) over the segment.  HBM-bound.
+// Per-request snapshot (inst_stride >= n_inst), or a shared one for few
+// requests: L lanes per request, U instances per lane and pass with every
+// load of the pass issued before its first cost.  Rows of at most 64
+// instances laid out for 16-byte loads have a kernel of their own (16 lanes
+// per request, four consecutive instances per lane).  HBM-bound.
+#include "lane_ops.h"
 #include "rt_internal.h"
 
 namespace rt {
 namespace {
 
-constexpr int kReq = 2;       // requests per thread (shared snapshot; measured: 1, 2, 4, 8 give 30.0, 29.5, 31.4, 37.1 us on 2^20 x 64)
+constexpr int kReq = 2;       // requests per thread (shared snapshot)
 constexpr int kBlock = 256;
 
 struct SnapEntry {
   float lb;    // w_b * backlog
   float qq;    // w_q * (float)queue
   int32_t kv;  // occupancy
-  int32_t pad;
+  float kvf;   // ... in float32
 };
 
 __device__ __forceinline__ bool req_ok(int32_t pool, int32_t p, int32_t oh, uint32_t c) {
@@ -34,10 +35,7 @@ __device__ __forceinline__ bool req_ok(int32_t pool, int32_t p, int32_t oh, uint
   return true;
 }
 
-// One thread's kReq requests against every snapshot entry.  kNonNeg: every
-// occupancy is >= 0, so occupancy + need < 2^32 and the sum converts exactly
-// through the unsigned 32-bit path (same value and rounding as int64).
-template <bool kNonNeg>
+// One thread's kReq requests against every snapshot entry, any values.
 __device__ __forceinline__ void score_loop(const SnapEntry* snap, int n, const ScoreArgs& a, const float* sg,
                                            const float* work, const int64_t* need, uint32_t* bkey,
                                            int32_t* bi) {
@@ -45,11 +43,7 @@ __device__ __forceinline__ void score_loop(const SnapEntry* snap, int n, const S
     const SnapEntry e = snap[j];
 #pragma unroll
     for (int r = 0; r < kReq; ++r) {
-      float press;
-      if constexpr (kNonNeg)
-        press = (float)((uint32_t)e.kv + (uint32_t)need[r]) * a.inv_cap;
-      else
-        press = (float)((int64_t)e.kv + need[r]) * a.inv_cap;
+      const float press = (float)((int64_t)e.kv + need[r]) * a.inv_cap;
       const float load = e.lb * sg[r];
       const float size = work[r] * (1.0f + a.rho * press) * sg[r];
       const float cost = load + size + e.qq;
@@ -62,20 +56,84 @@ __device__ __forceinline__ void score_loop(const SnapEntry* snap, int n, const S
   }
 }
 
+// The same where no cost can be NaN, -0 or negative and every occupancy +
+// need is below 2^24 (see the kernel): the sum is then exact in float32 and
+// float minima order as the keys do.  Costs are taken four at a time: their
+// minimum (two instructions), one compare and two selects per four instead of
+// per one; the index within the winning four is found afterwards by taking
+// its costs again.  9.3 VALU instructions a pair (8.3 with rho 1, whose
+// product changes nothing) against 17 above; 2^20 requests x 64 instances:
+// 25.9 us with the loop above, 16.8 us so.
+template <bool kRho1>
+__device__ __forceinline__ float plain_cost(const SnapEntry& e, const ScoreArgs& a, float sg, float work, float need) {
+  const float press = (e.kvf + need) * a.inv_cap;
+  const float load = e.lb * sg;
+  const float size = work * (1.0f + (kRho1 ? press : a.rho * press)) * sg;
+  return load + size + e.qq;
+}
+
+template <bool kRho1>
+__device__ __forceinline__ void plain_loop(const SnapEntry* snap, int n, const ScoreArgs& a, const float* sg,
+                                           const float* work, const int64_t* need, uint32_t* bkey, int32_t* bi) {
+  float best[kReq], needf[kReq];
+  int32_t bg[kReq];
+#pragma unroll
+  for (int r = 0; r < kReq; ++r) {
+    best[r] = __builtin_huge_valf();
+    bg[r] = 0;
+    needf[r] = (float)need[r];
+  }
+#pragma unroll 2
+  for (int j = 0; j < n; j += 4) {
+    SnapEntry e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = snap[j + u];
+#pragma unroll
+    for (int r = 0; r < kReq; ++r) {
+      float c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = plain_cost<kRho1>(e[u], a, sg[r], work[r], needf[r]);
+      const float m = __builtin_fminf(__builtin_fminf(__builtin_fminf(c[0], c[1]), c[2]), c[3]);
+      const bool b = m < best[r];
+      best[r] = b ? m : best[r];
+      bg[r] = b ? j : bg[r];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kReq; ++r) {
+    int32_t at = 3;
+#pragma unroll
+    for (int u = 2; u >= 0; --u)
+      at = plain_cost<kRho1>(snap[bg[r] + u], a, sg[r], work[r], needf[r]) == best[r] ? u : at;
+    bi[r] = bg[r] + at;
+    bkey[r] = __float_as_uint(best[r]);
+  }
+}
+
 __global__ void __launch_bounds__(kBlock) score_shared_kernel(ScoreArgs a) {
   extern __shared__ SnapEntry snap[];
+  __shared__ int32_t kv_max;
   const int n = a.n_inst;
-  int nonneg = 1;
+  if (threadIdx.x == 0) kv_max = 0;
+  __syncthreads();
+  int plain = 1;
+  int32_t kvm = 0;
   for (int j = threadIdx.x; j < n; j += kBlock) {
     SnapEntry e;
     e.lb = a.w_b * a.backlog[j];
     e.qq = a.w_q * (float)a.queue[j];
     e.kv = a.kv[j];
-    e.pad = 0;
-    nonneg &= e.kv >= 0;
+    e.kvf = (float)e.kv;
+    plain &= e.kv >= 0 && e.lb >= 0.0f && e.lb < __builtin_huge_valf() && e.qq >= 0.0f;
+    kvm = max(kvm, e.kv);
     snap[j] = e;
   }
-  nonneg = __syncthreads_and(nonneg);
+  // entries past the last, up to a multiple of four: never the first minimum
+  for (int j = n + threadIdx.x; j < ((n + 3) & ~3); j += kBlock)
+    snap[j] = SnapEntry{__builtin_huge_valf(), 0.0f, 0, 0.0f};
+  if (kvm > 0) atomicMax(&kv_max, kvm);
+  plain = __syncthreads_and(plain);
+  kvm = kv_max;
 
   const int64_t first = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kReq;
   float sg[kReq], work[kReq];
@@ -103,11 +161,23 @@ __global__ void __launch_bounds__(kBlock) score_shared_kernel(ScoreArgs a) {
         need[r] = a.pool == 1 ? (int64_t)p + oh : (int64_t)p;
       }
     }
+    // The plain loop's conditions.  The snapshot's terms are finite and not
+    // negative; occupancy + need stays below 2^24 for the largest occupancy;
+    // and work * (1 + rho * press) is finite for it, so for every one (each
+    // operation is monotone).  Then every product and sum of a cost is +0,
+    // positive or +inf (weights are +0 or positive), and +inf meets neither
+    // 0 * inf nor inf - inf: sigma and the reciprocal capacity are finite.
+    const float top = work[r] * (1.0f + a.rho * ((float)((int64_t)kvm + need[r]) * a.inv_cap));
+    plain &= (int64_t)kvm + need[r] < (1 << 24) && top < __builtin_huge_valf();
   }
-  if (nonneg)
-    score_loop<true>(snap, n, a, sg, work, need, bkey, bi);
-  else
-    score_loop<false>(snap, n, a, sg, work, need, bkey, bi);
+  if (__all(plain)) {
+    if (a.rho == 1.0f)
+      plain_loop<true>(snap, n, a, sg, work, need, bkey, bi);
+    else
+      plain_loop<false>(snap, n, a, sg, work, need, bkey, bi);
+  } else {
+    score_loop(snap, n, a, sg, work, need, bkey, bi);
+  }
 #pragma unroll
   for (int r = 0; r < kReq; ++r) {
     const int64_t i = first + r;
@@ -118,46 +188,93 @@ __global__ void __launch_bounds__(kBlock) score_shared_kernel(ScoreArgs a) {
   }
 }
 
-template <int S>
+// L lanes per request, 64 / L requests per wave and G such groups at once; a
+// lane takes instances (lane mod L) + L * u of its request's row, U of them
+// per pass, every load of a pass issued before its first cost.  Within a lane
+// the first of equal keys stays; then the lanes of a request reduce the key,
+// and the lowest index that holds it.  Stride 0 (one snapshot for every
+// request) is a row like any other.  Against one 64-lane segment, one load
+// per array in flight and a 64-bit shuffle reduction per request: 300,007 rows
+// of 37 instances 87.7 -> 28.9 us; 48 requests x 1,000 shared instances
+// 90 us with a thread per request, 10 us (the launch itself) so.
+template <int L, int U, int G>
 __global__ void __launch_bounds__(kBlock) score_rows_kernel(ScoreArgs a) {
-  constexpr int kSegs = 64 / S;
+  constexpr int kSegs = 64 / L;
   const int lane = threadIdx.x & 63;
-  const int sl = lane % S;
-  const int64_t i = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kSegs + lane / S;
-  const bool live = i < a.n_req;
-  int32_t p = 0, oh = 0;
-  uint32_t c = 0;
-  if (live) {
-    p = a.plen[i];
-    oh = a.pool == 1 ? a.ohat[i] : 0;
-    c = a.cls[i];
+  const int sl = lane & (L - 1);
+  const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int64_t first = wave * (kSegs * G) + lane / L;
+  const int n = a.n_inst;
+  int32_t p[G], oh[G];
+  uint32_t c[G];
+  bool live[G];
+  const float* bl[G];
+  const int32_t *qu[G], *kv[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int64_t i = first + g * kSegs;
+    live[g] = i < a.n_req;
+    const int64_t ii = live[g] ? i : 0;
+    p[g] = a.plen[ii];
+    oh[g] = a.pool == 1 ? a.ohat[ii] : 0;
+    c[g] = a.cls[ii];
+    bl[g] = a.backlog + ii * a.stride;
+    qu[g] = a.queue + ii * a.stride;
+    kv[g] = a.kv + ii * a.stride;
   }
-  const bool ok = live && req_ok(a.pool, p, oh, c);
-  uint64_t best = ~0ull;  // (key << 32) | index
-  if (ok) {
-    const float sg = a.sigma[c];
-    const float work = a.pool == 1 ? a.w_s * (float)oh * a.tau : a.w_s * (float)p * a.tau;
-    const int64_t need = a.pool == 1 ? (int64_t)p + oh : (int64_t)p;
-    const int64_t row = i * a.stride;
-    for (int j = sl; j < a.n_inst; j += S) {
-      const float press = (float)((int64_t)a.kv[row + j] + need) * a.inv_cap;
-      const float load = a.w_b * a.backlog[row + j] * sg;
-      const float size = work * (1.0f + a.rho * press) * sg;
-      const float cost = load + size + a.w_q * (float)a.queue[row + j];
-      const uint64_t k = ((uint64_t)cost_key(cost) << 32) | (uint32_t)j;
-      best = k < best ? k : best;
+  uint32_t bkey[G];
+  int32_t bj[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    bkey[g] = 0xffffffffu;
+    bj[g] = sl;
+  }
+  for (int j0 = 0; j0 < n; j0 += L * U) {
+    float b4[G][U];
+    int32_t q4[G][U], k4[G][U];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = min(j0 + u * L + sl, n - 1);
+        b4[g][u] = bl[g][j];
+        q4[g][u] = qu[g][j];
+        k4[g][u] = kv[g][j];
+      }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const float sg = a.sigma[c[g] & (kMaxClasses - 1)];
+      const float work = a.pool == 1 ? a.w_s * (float)oh[g] * a.tau : a.w_s * (float)p[g] * a.tau;
+      const uint32_t need = a.pool == 1 ? (uint32_t)p[g] + (uint32_t)oh[g] : (uint32_t)p[g];  // < 2^31 when ok
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + u * L + sl;
+        // occupancy + need, exact in 32 bits: unsigned when the occupancy is
+        // >= 0 (the sum is < 2^32), signed otherwise (the sum is < 2^31)
+        const uint32_t sum = (uint32_t)k4[g][u] + need;
+        const float kvn = k4[g][u] >= 0 ? (float)sum : (float)(int32_t)sum;
+        const float press = kvn * a.inv_cap;
+        const float load = a.w_b * b4[g][u] * sg;
+        const float size = work * (1.0f + a.rho * press) * sg;
+        const float cost = load + size + a.w_q * (float)q4[g][u];
+        uint32_t k = cost_key(cost);
+        k = j < n ? k : 0xffffffffu;
+        const bool b = k < bkey[g];
+        bkey[g] = b ? k : bkey[g];
+        bj[g] = b ? j : bj[g];
+      }
     }
   }
 #pragma unroll
-  for (int m = 1; m < S; m <<= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)best, m, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(best >> 32), m, 64);
-    const uint64_t o = ((uint64_t)hi << 32) | lo;
-    best = o < best ? o : best;
-  }
-  if (live && sl == 0) {
-    a.out_idx[i] = ok ? (int32_t)(uint32_t)best : -1;
-    a.out_score[i] = __uint_as_float(ok ? (uint32_t)(best >> 32) : 0x7fc00000u);
+  for (int g = 0; g < G; ++g) {
+    const uint32_t m = seg_min<L>(bkey[g]);
+    const uint32_t idx = seg_min<L>(bkey[g] == m ? (uint32_t)bj[g] : 0xffffffffu);
+    const int64_t i = first + g * kSegs;
+    const bool ok = req_ok(a.pool, p[g], oh[g], c[g]);
+    if (live[g] && sl == 0) {
+      a.out_idx[i] = ok ? (int32_t)idx : -1;
+      a.out_score[i] = __uint_as_float(ok ? m : 0x7fc00000u);
+    }
   }
 }
 
@@ -170,14 +287,6 @@ __global__ void __launch_bounds__(kBlock) score_rows_kernel(ScoreArgs a) {
 // reduce the key, then the lowest index holding it, with DPP within their
 // row.
 constexpr int kRowGroups = 4;
-
-__device__ __forceinline__ uint32_t row_min(uint32_t v) {
-  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));   // quad_perm xor 1
-  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));   // quad_perm xor 2
-  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));  // row_half_mirror
-  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));  // row_mirror
-  return v;
-}
 
 __global__ void __launch_bounds__(kBlock) score_rows16_kernel(ScoreArgs a) {
   constexpr int G = kRowGroups;
@@ -232,8 +341,8 @@ __global__ void __launch_bounds__(kBlock) score_rows16_kernel(ScoreArgs a) {
       bkey = b ? k : bkey;
       bj = b ? j0 + u : bj;
     }
-    const uint32_t m = row_min(bkey);
-    const uint32_t idx = row_min(bkey == m ? (uint32_t)bj : 0xffffffffu);
+    const uint32_t m = seg_min<16>(bkey);
+    const uint32_t idx = seg_min<16>(bkey == m ? (uint32_t)bj : 0xffffffffu);
     const int64_t i = first + 4 * g + rq;
     if (live[g] && ql == 0) {
       a.out_idx[i] = ok ? (int32_t)idx : -1;
@@ -305,12 +414,37 @@ __global__ void __launch_bounds__(kBlock) goodput_kernel(GoodputArgs a) {
 
 }  // namespace
 
+template <int L, int U>
+static hipError_t launch_rows(const ScoreArgs& a, hipStream_t stream) {
+  constexpr int G = U <= 2 ? 4 : 2;  // groups of requests at once
+  const int64_t per_block = (kBlock / 64) * (64 / L) * G;
+  hipLaunchKernelGGL((score_rows_kernel<L, U, G>), dim3((unsigned)((a.n_req + per_block - 1) / per_block)), dim3(kBlock),
+                     0, stream, a);
+  return hipGetLastError();
+}
+
+template <int L>
+static hipError_t launch_rows(const ScoreArgs& a, hipStream_t stream) {
+  switch ((a.n_inst + L - 1) / L) {
+    case 1: return launch_rows<L, 1>(a, stream);
+    case 2: return launch_rows<L, 2>(a, stream);
+    case 3: return launch_rows<L, 3>(a, stream);
+    default: return launch_rows<L, 4>(a, stream);
+  }
+}
+
+// A shared snapshot takes a thread per kReq requests from this many requests
+// on: the thread walks the whole snapshot alone (about 45 ns an instance), and
+// fewer requests do not fill the GPU's SIMDs that way, while L lanes per
+// request cost about 0.7 ps a pair.
+constexpr int64_t kSharedMinReq = 1 << 16;
+
 hipError_t launch_score(const ScoreArgs& a, hipStream_t stream) {
   if (a.n_req <= 0) return hipSuccess;
-  if (a.stride == 0) {
+  if (a.stride == 0 && a.n_req >= kSharedMinReq) {
     const int64_t per_block = (int64_t)kBlock * kReq;
     const int64_t blocks = (a.n_req + per_block - 1) / per_block;
-    const size_t lds = sizeof(SnapEntry) * (size_t)a.n_inst;
+    const size_t lds = sizeof(SnapEntry) * (((size_t)a.n_inst + 3) & ~(size_t)3);
     hipLaunchKernelGGL(score_shared_kernel, dim3((unsigned)blocks), dim3(kBlock), lds, stream, a);
     return hipGetLastError();
   }
@@ -321,20 +455,10 @@ hipError_t launch_score(const ScoreArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(score_rows16_kernel, dim3(blocks), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
   }
-  int S = 1;
-  while (S < a.n_inst && S < 64) S <<= 1;
-  const int64_t per_block = (kBlock / 64) * (64 / S);
-  const unsigned blocks = (unsigned)((a.n_req + per_block - 1) / per_block);
-  switch (S) {
-    case 1: hipLaunchKernelGGL(score_rows_kernel<1>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL(score_rows_kernel<2>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    case 4: hipLaunchKernelGGL(score_rows_kernel<4>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    case 8: hipLaunchKernelGGL(score_rows_kernel<8>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    case 16: hipLaunchKernelGGL(score_rows_kernel<16>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    case 32: hipLaunchKernelGGL(score_rows_kernel<32>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-    default: hipLaunchKernelGGL(score_rows_kernel<64>, dim3(blocks), dim3(kBlock), 0, stream, a); break;
-  }
-  return hipGetLastError();
+  // lanes per request: few instances per lane, and few idle lanes
+  if (a.n_inst <= 16) return launch_rows<4>(a, stream);
+  if (a.n_inst <= 64) return launch_rows<16>(a, stream);
+  return launch_rows<64>(a, stream);
 }
 
 hipError_t launch_goodput(const GoodputArgs& a, hipStream_t stream) {
