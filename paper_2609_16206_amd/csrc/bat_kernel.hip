@@ -22,11 +22,13 @@
 // arrival scheduled.  So every instance's events up to an arrival can be
 // taken prefill pool first, then decode pool, each instance in time order:
 // every instance sees the same sequence of events, in the same order and
-// with the same arithmetic, as a global time-ordered loop.  Two kernels do
+// with the same arithmetic, as a global time-ordered loop.  Three kernels do
 // this: bseg_kernel (below), one replica per segment of S <= 64 lanes and M
 // instances per lane in registers (M = 1 for points with P + D <= 64, M = 2
-// for pools of up to 128 instances); and bat_kernel, one replica per lane
-// walking its instances in turn, for any point.  Batch members and KV
+// for pools of up to 128 instances); bwide_kernel, one replica per workgroup of
+// four or eight waves, for pools beyond that; and bat_kernel, one replica per
+// lane walking its instances in turn, for the widest points (both pools
+// together above about 1,500 instances).  Batch members and KV
 // transfers in flight are sorted rings in scratch, contiguous per instance.
 //
 // Arithmetic.  Times are float64 ns; every operation matches the written
@@ -982,6 +984,385 @@ __global__ __launch_bounds__(kBlock, kMinBlocks) void bseg_kernel(SimArgs a, Bat
   if (flag) atomicOr(a.flag, flag);
 }
 
+// ---------------------------------------------------------------------------
+// Wide variant: one replica per workgroup of W waves, M instances per lane in
+// registers as in the segment variant, for pools beyond its 128 instances.
+// Instances are dealt to the waves round robin (instance j of a pool to wave
+// j mod W; in a wave the first lanes hold prefill instances and the next ones
+// decode instances).  A prefill instance evolves alone and a decode instance
+// needs nothing but its landings, so each wave runs the rounds of its own
+// instances for itself: prefill rounds, whose departures it leaves in a list
+// of its own in LDS; a barrier; every wave takes the transfers to its decode
+// instances from all lists; decode rounds; score, one 64-bit LDS minimum per
+// pool (cost key, instance index); a barrier; and the winners' lanes admit.
+// Two barriers a step, none inside a round.
+//
+// The request is the same on every lane, and so is every branch around a
+// barrier.  What passes between waves through memory (a request's prefill end,
+// parked in its span slot) is written before the first barrier of a step and
+// read after it.
+//
+// What bounds it: a step's chain of events and its two barriers.  64 replicas
+// of 32 + 256 instances x 400 requests: 92 ms with one replica per lane
+// (bat_kernel, which walks the 288 instances one after the other in scratch),
+// 1.10 ms so; 256 of 128 + 1,024 x 60: 80 and 1.6 ms; 32,768 of 1 + 130 x 40,
+// enough for every lane of bat_kernel: 9.7 and 7.2 ms.
+// Departures a wave lists before they are taken.  One round adds at most one
+// per prefill instance of the wave, which is no more (so a list that is taken
+// always has room for the next round).
+constexpr int kDepart = 128;
+
+struct Depart {
+  double land, end;      // when the KV lands, when prefill ended
+  int32_t r, d;          // request, decode instance
+  int32_t p, o, oh, pad;
+};
+
+template <int W, int M>
+__global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) {
+  static_assert((kMaxPool / W < 64 * M ? kMaxPool / W : 64 * M) <= kDepart, "one round's departures fit a wave's list");
+  const int lane = (int)(threadIdx.x & 63);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int32_t rep = a.work[blockIdx.x];
+  const int64_t lo = a.offsets[rep];
+  const int32_t len = (int32_t)(a.offsets[rep + 1] - lo);
+  const DevPoint& pt = a.points[a.param_point ? a.param_point[rep] : 0];
+  const int32_t P = pt.P, D = pt.D;
+  const int32_t LPW = wide_pool_lanes(P, M, W), LDW = wide_pool_lanes(D, M, W);
+  const bool isP = lane < LPW, isD = lane >= LPW && lane < LPW + LDW;
+  const int32_t nP = max(0, (P - wave + W - 1) / W);  // prefill instances of the wave
+  const int32_t lrel = isP ? lane : lane - LPW;
+  const int32_t npool = isP ? P : D;
+  const int32_t C = b.C;
+  int32_t jj[M];  // the slots' instances; -1: none
+  Entry* rings[M];
+  Entry* wrings[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int32_t j = wave + W * (lrel * M + m);
+    jj[m] = (isP || isD) && j < npool ? j : -1;
+    const int64_t slot = (int64_t)blockIdx.x * b.NI + (jj[m] < 0 ? 0 : (isP ? 0 : P) + j);
+    rings[m] = reinterpret_cast<Entry*>(b.ring) + slot * C;
+    wrings[m] = reinterpret_cast<Entry*>(b.wring) + slot * C;
+  }
+  const double beta = isP ? pt.beta_pre : pt.beta_dec;
+  const double xfer = (double)pt.xfer_tok_ns;
+  const int32_t ncls = pt.n_classes, pol = pt.policy, len_thr = pt.len_thr, bmode = pt.mode;
+  const float w_b = pt.w_b, w_s = pt.w_s, w_q = pt.w_q, rho = pt.rho;
+  const float tau = isP ? pt.tau_pre : pt.tau_dec, basec = isP ? pt.pre_base : 0.0f;
+  const float inv = isP ? pt.inv_cap_pre : pt.inv_cap_dec;
+  const double pre_base_ns = (double)pt.pre_base_ns, pre_tok_ns = (double)pt.pre_tok_ns;
+  const double dec_tok_ns = (double)pt.dec_tok_ns;
+  const bool samp = pol == kPolicyLearnedSampled;
+
+  __shared__ Depart dep[W][kDepart];
+  __shared__ int32_t dep_n[W];           // entries of each wave's list; + kDepart + 1: more to come
+  __shared__ unsigned long long best[2][2];  // per step parity and pool: (cost key << 32) | instance
+  __shared__ int32_t stop;               // a ring overflowed
+  __shared__ float sig[kMaxClasses];
+  if (threadIdx.x < kMaxClasses) sig[threadIdx.x] = pt.sigma[threadIdx.x];
+  if (threadIdx.x < 4) best[threadIdx.x >> 1][threadIdx.x & 1] = ~0ull;
+  if (threadIdx.x == 0) stop = 0;
+  __syncthreads();
+
+  BInst in[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) init_binst(in[m]);
+  double tmax = 0.0;
+  bool rej = false, full = false;
+  int64_t last = -1;
+
+  auto next_done = [&](const BInst& x) __attribute__((always_inline)) {  // the batch's next completion
+    double rem = x.bw.k0 - x.v;
+    rem = rem < 0.0 ? 0.0 : rem;
+    return x.nact > 0 ? x.tl + rem * slowdown(beta, x.nact) : kInf;
+  };
+  auto clock_to = [&](BInst& x, double t) __attribute__((always_inline)) {
+    if (x.nact > 0) {
+      const double dv = (t - x.tl) / slowdown(beta, x.nact);
+      x.v = x.v + dv;
+      x.left = x.left - (double)x.nact * dv;
+    }
+    x.tl = t;
+  };
+  // The front leaves the batch at time tc; the next front's data follow.
+  auto leave = [&](BInst& x, const Entry* rg, double tc) __attribute__((always_inline)) {
+    x.left = x.left - (double)x.nact * (x.bw.k0 - x.v);
+    x.v = x.bw.k0;
+    x.tl = tc;
+    tmax = fmax(tmax, tc);
+    x.q -= 1;
+    x.head += 1;
+    x.nact -= 1;
+    if (x.nact == 0) {
+      x.left = 0.0;
+    } else {
+      window_pop(x.bw, rg, C, x.head, x.nact);
+      const int64_t g = lo + x.bw.r0;
+      x.p0 = a.plen[g];
+      x.o0 = a.olen[g];
+      x.oh0 = a.ohat[g];
+      if (isP) {
+        x.x0 = i64_to_f64(a.arrival[g]);
+        x.dst0 = a.i_dec[g];
+      } else {
+        x.x0 = __longlong_as_double(a.span[g]);
+      }
+    }
+  };
+
+  // Prefill rounds up to `now` until no instance of the wave has an event, or
+  // its list may not hold another round's departures; returns the list's
+  // count (+ kDepart + 1 in the second case).
+  auto prefill_rounds = [&](double now) -> int32_t {
+    int32_t n = 0;
+    for (;;) {
+      if (n + nP > kDepart) return n + kDepart + 1;
+      uint64_t any = 0;
+      static_for<M>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        BInst& x = in[m];
+        const double tc = next_done(x);
+        const bool fire = isP && tc <= now && x.nact > 0;
+        const uint64_t fm = __ballot(fire);
+        any |= fm;
+        if (fire) {
+          const int64_t g = lo + x.bw.r0;
+          const double land = tc + (double)x.p0 * xfer;
+          a.ttft[g] = round_ns(tc - x.x0);
+          a.span[g] = __double_as_longlong(tc);
+          tmax = fmax(tmax, land);
+          dep[wave][n + __popcll(fm & ((1ull << lane) - 1ull))] =
+              Depart{land, tc, x.bw.r0, x.dst0, x.p0, x.o0, x.oh0, 0};
+          x.kv = x.kv - (double)x.p0;
+          x.pend = x.pend - (double)x.p0;
+          leave(x, rings[m], tc);
+        }
+        n += __popcll(fm);
+      });
+      if (any == 0) return n;
+    }
+  };
+  // The listed transfers to this lane's decode instances.
+  auto take_transfers = [&](int w, int32_t n) {
+    for (int32_t i = 0; i < n; ++i) {
+      const int32_t d = dep[w][i].d;
+      static_for<M>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        BInst& y = in[m];
+        if (isD && d == jj[m]) {
+          const Depart e = dep[w][i];
+          const int32_t at = ring_put(wrings[m], C, y.wh, y.nw, e.land, e.r, y.wtail, full);
+          if (at >= 0) {
+            window_put(y.tw, at, y.wh, e.land, e.r);
+            if (at == y.wh) {
+              y.pf1 = e.end;
+              y.p1 = e.p;
+              y.o1 = e.o;
+              y.oh1 = e.oh;
+            }
+            y.nw += 1;
+          }
+        }
+      });
+    }
+  };
+  auto decode_rounds = [&](double now) {
+    for (;;) {
+      bool anyf = false;
+      static_for<M>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        BInst& x = in[m];
+        const double tc = next_done(x);
+        const double tj = x.nw > 0 ? x.tw.k0 : kInf;
+        const bool fire = isD && (x.nact > 0 || x.nw > 0) && (tc <= tj ? tc : tj) <= now;
+        anyf = anyf || fire;
+        if (!fire) return;
+        if (tc <= tj) {
+          const int64_t g = lo + x.bw.r0;
+          a.span[g] = round_ns(tc - x.x0);
+          x.kv = x.kv - ((double)x.p0 + (double)x.o0);
+          x.pend = x.pend - (double)x.oh0;
+          leave(x, rings[m], tc);
+        } else {
+          const int32_t r = x.tw.r0, pr = x.p1, orr = x.o1, ohr = x.oh1;
+          const double pfr = x.pf1;
+          x.wh += 1;
+          x.nw -= 1;
+          if (x.nw > 0) {
+            window_pop(x.tw, wrings[m], C, x.wh, x.nw);
+            const int64_t g = lo + x.tw.r0;
+            x.p1 = a.plen[g];
+            x.o1 = a.olen[g];
+            x.oh1 = a.ohat[g];
+            x.pf1 = __longlong_as_double(a.span[g]);
+          }
+          clock_to(x, tj);
+          const double w = (double)(orr - 1) * dec_tok_ns;
+          x.owed = x.owed - w;
+          const double f = x.v + w;
+          const int32_t at = ring_put(rings[m], C, x.head, x.nact, f, r, x.btail, full);
+          if (at >= 0) {
+            window_put(x.bw, at, x.head, f, r);
+            if (at == x.head) {
+              x.x0 = pfr;
+              x.p0 = pr;
+              x.o0 = orr;
+              x.oh0 = ohr;
+            }
+            x.nact += 1;
+            x.left = x.left + w;
+          }
+        }
+      });
+      if (!__any(anyf)) return;
+    }
+  };
+  // Every event up to `now`, on every instance of the replica.
+  auto run_to = [&](double now) {
+    for (;;) {
+      const int32_t n = prefill_rounds(now);
+      if (lane == 0) dep_n[wave] = n;
+      __syncthreads();
+      bool more = false;
+      for (int w = 0; w < W; ++w) {
+        const int32_t c = dep_n[w];
+        more = more || c > kDepart;
+        take_transfers(w, c > kDepart ? c - (kDepart + 1) : c);
+      }
+      if (!more) break;
+      __syncthreads();  // every wave has taken the lists
+    }
+    decode_rounds(now);
+  };
+
+  auto fetch = [&](int32_t t) {
+    const int64_t g = lo + min(t, len - 1);
+    Req q0;
+    q0.arr = a.arrival[g];
+    q0.p = a.plen[g];
+    q0.o = a.olen[g];
+    q0.oh = a.ohat[g];
+    q0.c = a.cls[g];
+    q0.ws = samp ? *reinterpret_cast<const uint4*>(a.samp + 4 * g) : make_uint4(0u, 0u, 0u, 0u);
+    return q0;
+  };
+  Req nx = fetch(0);
+  bool dead = false;
+  int par = 0;  // parity of the admitted requests (the argmin cells alternate)
+  for (int32_t t = 0; t < len && !dead; ++t) {
+    const Req cur = nx;
+    nx = fetch(t + 1);
+    const int64_t arr = cur.arr;
+    const int32_t p = cur.p, o = cur.o, oh = cur.oh;
+    const uint32_t c = cur.c;
+    const int64_t g = lo + t;
+    const bool valid = p >= 1 && o >= 1 && oh >= 1 && (int64_t)p + o <= INT32_MAX && (int64_t)p + oh <= INT32_MAX &&
+                       (int32_t)c < ncls && arr >= 0 && arr >= last;
+    if (__builtin_amdgcn_readfirstlane((int)valid) == 0) {  // (the same on every lane)
+      rej = true;
+      if (threadIdx.x == 0) {
+        a.i_pre[g] = a.i_dec[g] = -1;
+        a.ttft[g] = a.span[g] = -1;
+      }
+      continue;
+    }
+    last = arr;
+    const double now = i64_to_f64(arr);
+    tmax = fmax(tmax, now);
+    run_to(now);
+    // (every wave is past the last step's reads of these cells)
+    if (threadIdx.x < 2) best[par ^ 1][threadIdx.x] = ~0ull;
+    // each lane's key: the lowest of its instances' (the lowest index on
+    // equal keys), on every clock brought to the arrival
+    uint32_t bkey = 0xffffffffu;
+    int32_t bj = -1;
+    const uint32_t u = isP ? cur.ws.x : cur.ws.z, w2 = isP ? cur.ws.y : cur.ws.w;
+    const uint32_t c1 = __umulhi(u, (uint32_t)npool), cx = __umulhi(w2, (uint32_t)(npool - 1));
+    const uint32_t c2 = npool > 1 ? cx + (cx >= c1 ? 1u : 0u) : c1;
+    const float sg = sig[c];
+    const float work = isP ? w_s * (float)p * tau : w_s * (float)oh * tau;
+    const double need = isP ? (double)p : (double)p + (double)oh;
+    static_for<M>([&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value;
+      BInst& x = in[m];
+      if (jj[m] < 0) return;
+      clock_to(x, now);
+      const int32_t j = jj[m];
+      uint32_t key;
+      if (pol == kPolicyRoundRobin) {
+        key = j == t % npool ? 0u : 1u;
+      } else if (pol == kPolicyLeastLoaded) {
+        key = (uint32_t)x.q;
+      } else if (pol == kPolicyLengthThreshold) {
+        const bool part = isP || npool == 1 || ((j >= (npool + 1) / 2) == (oh >= len_thr));
+        key = part ? (uint32_t)x.q : 0xffffffffu;
+      } else {
+        float bl;
+        if (bmode == 0) {
+          double w = x.left < 0.0 ? 0.0 : x.left;
+          w = w + x.owed;
+          bl = (float)w * 1e-9f;
+        } else if (isP) {
+          bl = tau * (float)x.pend + basec * (float)x.q;
+        } else {
+          bl = tau * (float)x.pend;
+        }
+        const float press = (float)(x.kv + need) * inv;
+        const float load = w_b * bl * sg;
+        const float size = work * (1.0f + rho * press) * sg;
+        key = cost_key(load + size + w_q * (float)x.q);
+        if (samp) key = ((uint32_t)j == c1 || (uint32_t)j == c2) ? key : 0xffffffffu;
+      }
+      const bool lower = m == 0 || key < bkey;
+      bkey = lower ? key : bkey;
+      bj = lower ? j : bj;
+    });
+    if (bj >= 0) atomicMin(&best[par][isP ? 0 : 1], ((unsigned long long)bkey << 32) | (uint32_t)bj);
+    if (full) stop = 1;
+    __syncthreads();
+    const int32_t ip = (int32_t)(uint32_t)best[par][0], id = (int32_t)(uint32_t)best[par][1];
+    dead = stop != 0;
+    par ^= 1;
+    static_for<M>([&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value;
+      BInst& x = in[m];
+      if (isP && jj[m] == ip) {
+        a.i_pre[g] = ip;
+        a.i_dec[g] = id;
+        const double w = pre_base_ns + (double)p * pre_tok_ns;
+        const double f = x.v + w;
+        const int32_t at = ring_put(rings[m], C, x.head, x.nact, f, t, x.btail, full);
+        if (at >= 0) {
+          window_put(x.bw, at, x.head, f, t);
+          if (at == x.head) {
+            x.x0 = now;
+            x.p0 = p;
+            x.o0 = o;
+            x.oh0 = oh;
+            x.dst0 = id;
+          }
+          x.nact += 1;
+          x.q += 1;
+          x.kv = x.kv + (double)p;
+          x.pend = x.pend + (double)p;
+          x.left = x.left + w;
+        }
+      }
+      if (isD && jj[m] == id) {
+        x.owed = x.owed + (double)(o - 1) * dec_tok_ns;
+        x.q += 1;
+        x.kv = x.kv + ((double)p + (double)o);
+        x.pend = x.pend + (double)oh;
+      }
+    });
+  }
+  if (!dead) run_to(kInf);
+  const uint32_t flag = (tmax >= kTimeLimit ? kFlagTimeRange : 0u) | (rej ? kFlagRejected : 0u) |
+                        (full ? kFlagBatchCap : 0u);
+  if (flag) atomicOr(a.flag, flag);
+}
+
 }  // namespace bat
 
 // One allocation, 256-byte aligned arrays: the ten state arrays, then the
@@ -1046,6 +1427,13 @@ hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, 
   }
   RT_BSEG_FOR_EACH(RT_BSEG_CASE)
 #undef RT_BSEG_CASE
+#define RT_BWIDE_CASE(W_, M_)                                                                                      \
+  if (c.S == 64 * W_ && c.MP == M_) {                                                                              \
+    hipLaunchKernelGGL((bat::bwide_kernel<W_, M_>), dim3((unsigned)a.n_work), dim3(64 * W_), 0, stream, a, b);     \
+    return hipGetLastError();                                                                                      \
+  }
+  RT_BWIDE_FOR_EACH(RT_BWIDE_CASE)
+#undef RT_BWIDE_CASE
   // one replica per lane: replicas per wave a power of two, at most 64, so
   // that the launch has about one wave per SIMD (1,024) where it can
   // (measured on 16,384 replicas of 72 instances: 64 per wave 270 ms, 16
@@ -1057,11 +1445,10 @@ hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, 
   return hipGetLastError();
 }
 
-// Lanes a launch of class c over n_work replicas spans (the scratch owners;
-// the one-replica-per-lane kernel numbers its replicas densely, so n_work of
-// them fit).
+// Scratch owners of a launch of class c over n_work replicas: the lanes of a
+// segment class, the replicas of the others.
 int64_t bat_lanes(const SimClass& c, int64_t n_work) {
-  const int64_t lanes = n_work * (int64_t)c.S;
+  const int64_t lanes = n_work * (int64_t)(c.S > 64 ? 1 : c.S);
   return (lanes + bat::kBlock - 1) / bat::kBlock * bat::kBlock;
 }
 

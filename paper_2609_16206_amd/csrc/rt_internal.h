@@ -24,6 +24,12 @@ struct DevPoint {
   double beta_pre, beta_dec;  // batched service: slowdown per extra member
 };
 
+constexpr int kMaxPool = 1024;  // RT_MAX_POOL
+
+// Lanes per wave holding a pool of n instances, dealt round robin to W waves
+// at M per lane.
+__host__ __device__ inline int wide_pool_lanes(int n, int M, int W) { return ((n + W - 1) / W + M - 1) / M; }
+
 enum : uint32_t { kFlagRejected = 1u, kFlagBadTrace = 2u, kFlagTimeRange = 4u, kFlagBatchCap = 8u };
 
 // rt_policy values as the kernels read them from DevPoint::policy.
@@ -117,11 +123,14 @@ struct BatScratch {
 size_t bat_scratch_bytes(int64_t S, int32_t NI, int32_t C);
 BatScratch bat_scratch_carve(char* base, int64_t S, int32_t NI, int32_t C);
 // Batched classes {S, M}: one replica per aligned segment of S lanes, M
-// instances per lane (ceil(P / M) + ceil(D / M) <= S; MP = MD = M), then the
+// instances per lane (ceil(P / M) + ceil(D / M) <= S; MP = MD = M); then one
+// replica per workgroup of W waves, M instances per lane (S = 64 W); then the
 // general one, one replica per lane (S = 1, MP = MD = 0).  bat_lanes: the
-// lanes a launch spans, each the owner of NI state slots and NI ring pairs in
-// the class's scratch (NI = M for a segment class).
+// scratch owners of a launch, each with NI state slots and NI ring pairs
+// (segment classes: lanes, NI = M; the others: replicas, NI = the largest
+// P + D).
 #define RT_BSEG_FOR_EACH(X) X(4, 1) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2)
+#define RT_BWIDE_FOR_EACH(X) X(4, 1) X(8, 1) X(8, 2) X(8, 3)
 hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, hipStream_t stream);
 int64_t bat_lanes(const SimClass& c, int64_t n_work);
 

@@ -32,10 +32,13 @@ constexpr int kModes[] = {kModeTrue, kModeProxy, kModeBase, kModeTrueSampled, kM
 constexpr int kNumModes = (int)(sizeof(kModes) / sizeof(kModes[0]));
 
 // Batched-service shapes {S, M}: the segment ones (one instance per lane
-// first, then two), then the general one-replica-per-lane class {1, 0}.
+// first, then two), the multi-wave ones, then the general
+// one-replica-per-lane class {1, 0}.
 #define RT_BSEG_SHAPE(S_, M_) {S_, M_},
-const SegShape kBatShapes[] = {RT_BSEG_FOR_EACH(RT_BSEG_SHAPE){1, 0}};
+#define RT_BWIDE_SHAPE(W_, M_) {64 * W_, M_},
+const SegShape kBatShapes[] = {RT_BSEG_FOR_EACH(RT_BSEG_SHAPE) RT_BWIDE_FOR_EACH(RT_BWIDE_SHAPE){1, 0}};
 #undef RT_BSEG_SHAPE
+#undef RT_BWIDE_SHAPE
 constexpr int kNumBat = (int)(sizeof(kBatShapes) / sizeof(kBatShapes[0]));
 
 }  // namespace

@@ -75,10 +75,6 @@
 namespace rt {
 namespace seg {
 
-// Lanes per wave holding a pool of n instances, dealt round robin to W waves
-// at M per lane.
-__host__ __device__ inline int wide_pool_lanes(int n, int M, int W) { return ((n + W - 1) / W + M - 1) / M; }
-
 __device__ __forceinline__ double rl_f64(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
