@@ -81,7 +81,7 @@ def _source_hash(files):
 SIM_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in (
     "seg_kernel.h", "lseg_kernel.h", "wseg_kernel.h", "seg_true.hip", "seg_proxy.hip", "seg_base.hip", "seg_true_s.hip", "seg_proxy_s.hip", "seg_classes.hip",
     "lane_ops.h", "rt_internal.h", "api.hip")]
-BAT_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in ("bat_kernel.hip", "lane_ops.h", "rt_internal.h", "api.hip", "seg_classes.hip")]
+BAT_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in ("bat_kernel.hip", "lbat_kernel.h", "lane_ops.h", "rt_internal.h", "api.hip", "seg_classes.hip")]
 SCORE_SOURCES = ["paper_2609_16206_amd/csrc/score_kernel.hip", "paper_2609_16206_amd/csrc/rt_internal.h"]
 
 
@@ -210,7 +210,7 @@ def bench_sim(args):
                                                                                           SIM_SOURCES)
     roof["valu_busy_pct"] = (_valu_busy("bat", args.workload, BAT_SOURCES) if batched else
                              _valu_busy("sim", args.workload, SIM_SOURCES))
-    roof["kernel"] = ("rt::bat::bseg_kernel / bat_kernel (the batched classes the call launches)" if batched else
+    roof["kernel"] = ("rt::bat::lbat_kernel / bwide_kernel / bat_kernel (the batched classes the call launches)" if batched else
                       "rt::seg::lseg_kernel / seg_kernel / wseg_kernel (every class one rt_sim_run_replicas call launches)")
     roof["per_unit"] = (f"{SIM_BYTES_PER_REQ} B/request; {SIM_OPS_PER_PAIR} lane-ops/pair + {SIM_OPS_PER_REQ}/request "
                         f"(recount {RECOUNT_SIM[0]}/pair + {RECOUNT_SIM[1]}/request)")

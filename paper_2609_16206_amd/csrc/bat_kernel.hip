@@ -23,13 +23,14 @@
 // taken prefill pool first, then decode pool, each instance in time order:
 // every instance sees the same sequence of events, in the same order and
 // with the same arithmetic, as a global time-ordered loop.  Three kernels do
-// this: bseg_kernel (below), one replica per segment of S <= 64 lanes and M
-// instances per lane in registers (M = 1 for points with P + D <= 64, M = 2
-// for pools of up to 128 instances); bwide_kernel, one replica per workgroup of
-// four or eight waves, for pools beyond that; and bat_kernel, one replica per
-// lane walking its instances in turn, for the widest points (both pools
-// together above about 1,500 instances).  Batch members and KV
-// transfers in flight are sorted rings in scratch, contiguous per instance.
+// this: lbat_kernel (lbat_kernel.h), one replica per segment of S <= 64 lanes
+// and M instances per lane in registers, queues in LDS (M = 1 for points with
+// P + D <= 64, M = 2 for pools of up to 128 instances); bwide_kernel, one
+// replica per workgroup of four or eight waves, for pools beyond that; and
+// bat_kernel, one replica per lane walking its instances in turn, for the
+// widest points (both pools together above about 1,500 instances).  In the
+// last two batch members and KV transfers in flight are sorted rings in
+// scratch, contiguous per instance.
 //
 // Arithmetic.  Times are float64 ns; every operation matches the written
 // model one for one (built with -ffp-contract=off): s = 1 + beta * (b - 1),
@@ -432,23 +433,6 @@ __global__ __launch_bounds__(kBlock) void bat_kernel(SimArgs a, BatScratch b, in
 }
 
 
-// ---------------------------------------------------------------------------
-// Segment variant: one replica per aligned segment of S lanes of a wave, one
-// instance per lane (prefill instances on lanes [0, P), decode instances on
-// [P, P + D)), as in the serial segment kernels.  A lane's instance state and
-// the front entries of its rings (with the front request's data) live in its
-// registers; the rings behind the fronts are the lane's own scratch.  Every
-// step (one request of every segment's replica) runs wave-uniform rounds:
-// prefill rounds, in each of which every prefill lane whose front completes
-// by the arrival lets it go and the decode lanes of the segment take the
-// departing KV transfers from it (read with cross-lane shuffles); decode
-// rounds, in each of which every decode lane takes its next event (a
-// completion, or a KV landing joining its batch); then every instance's clock
-// is brought to the arrival, every lane scores its instance, the two argmins
-// are DPP reductions over the segment, and the chosen lanes admit.  A round
-// pops one member per lane: members with equal finish virtual times leave in
-// consecutive rounds at the same time, with the same arithmetic as leaving
-// together (the remaining work they see is 0).
 struct RingTail {
   double t;
   int32_t r;
@@ -521,7 +505,7 @@ struct Req {
   uint4 ws;
 };
 
-// One instance of the segment kernel, in registers (a lane holds M): the
+// One instance of the wide kernel, in registers (a lane holds M): the
 // batch's state, the first two entries of its rings with the front
 // requests' data, and the rings' cached tails.
 struct BInst {
@@ -552,441 +536,9 @@ __device__ __forceinline__ void init_binst(BInst& x) {
   x.wtail = RingTail{0.0, 0};
 }
 
-// kMinBlocks: workgroups per compute unit the register budget must allow
-// (1: as many registers as the kernel wants, for launches whose waves do not
-// fill the GPU; 3 (M = 1) or 2 (M = 2): three or two waves per SIMD, for
-// launches with many waves).  M: instances per lane (prefill instance j on
-// lane j / M, slot j % M; decode instance d on lane ceil(P / M) + d / M,
-// slot d % M).  A round takes at most one event of every instance, slot
-// after slot; the state of every slot stays in registers (about 46 each).
-template <int S, int kMinBlocks, int M>
-__global__ __launch_bounds__(kBlock, kMinBlocks) void bseg_kernel(SimArgs a, BatScratch b) {
-  const int lane = (int)(threadIdx.x & 63);
-  const int64_t gl = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int sl = lane & (S - 1);
-  const int base = lane & ~(S - 1);
-  const int64_t seg = gl / S;
-  const bool has = seg < a.n_work;
-  const int32_t rep = has ? a.work[seg] : 0;
-  const int64_t lo = has ? a.offsets[rep] : 0;
-  const int64_t len = has ? a.offsets[rep + 1] - lo : 0;
-  const DevPoint& pt = a.points[(has && a.param_point) ? a.param_point[rep] : 0];
-  const int32_t P = pt.P, D = pt.D;
-  const int32_t LP = (P + M - 1) / M, LD = (D + M - 1) / M;  // lanes holding each pool
-  const bool isP = has && sl < LP;
-  const bool isD = has && sl >= LP && sl < LP + LD;
-  const int32_t j0 = (isP ? sl : sl - LP) * M;  // the lane's first instance in its pool
-  bool ok[M];                                    // slot m holds an instance
-#pragma unroll
-  for (int m = 0; m < M; ++m) ok[m] = (isP && j0 + m < P) || (isD && j0 + m < D);
-  const double beta = isP ? pt.beta_pre : pt.beta_dec;
-  const double xfer = (double)pt.xfer_tok_ns;
-  const bool samp = pt.policy == kPolicyLearnedSampled;
-  // The point's parameters, read once: the loop's stores could alias them,
-  // so reads inside it would be repeated, each with a wait for every memory
-  // access still outstanding.
-  const int32_t ncls = pt.n_classes, pol = pt.policy, len_thr = pt.len_thr, bmode = pt.mode;
-  const float w_b = pt.w_b, w_s = pt.w_s, w_q = pt.w_q, rho = pt.rho;
-  const float tau_pre = pt.tau_pre, tau_dec = pt.tau_dec, pre_base = pt.pre_base;
-  const float inv = isP ? pt.inv_cap_pre : pt.inv_cap_dec;
-  const double pre_base_ns = (double)pt.pre_base_ns, pre_tok_ns = (double)pt.pre_tok_ns;
-  const double dec_tok_ns = (double)pt.dec_tok_ns;
-  // sigma per class of each segment's point (LDS)
-  __shared__ float sig[(kBlock / S) * kMaxClasses];
-  const int sblk = (int)(threadIdx.x / S);
-  for (int k = sl; k < kMaxClasses; k += S) sig[sblk * kMaxClasses + k] = pt.sigma[k];
-  __syncthreads();
-  const int32_t C = b.C;
-  // the rings of slot m: batch members and KV transfers in flight
-  Entry* rings[M];
-  Entry* wrings[M];
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    rings[m] = reinterpret_cast<Entry*>(b.ring) + (gl * M + m) * (int64_t)C;
-    wrings[m] = reinterpret_cast<Entry*>(b.wring) + (gl * M + m) * (int64_t)C;
-  }
-
-  BInst in[M];
-#pragma unroll
-  for (int m = 0; m < M; ++m) init_binst(in[m]);
-  double tmax = 0.0;
-  bool rej = false, full = false, dead = false;
-  int64_t last = -1;
-
-  // The data of a batch's new front (needed only when it leaves).
-  auto front_data = [&](BInst& x) __attribute__((always_inline)) {
-    const int64_t g = lo + x.bw.r0;
-    x.p0 = a.plen[g];
-    x.o0 = a.olen[g];
-    x.oh0 = a.ohat[g];
-    if (isP) {
-      x.x0 = i64_to_f64(a.arrival[g]);
-      x.dst0 = a.i_dec[g];
-    } else {
-      x.x0 = __longlong_as_double(a.span[g]);
-    }
-  };
-  auto transfer_data = [&](BInst& x) __attribute__((always_inline)) {
-    const int64_t g = lo + x.tw.r0;
-    x.p1 = a.plen[g];
-    x.o1 = a.olen[g];
-    x.oh1 = a.ohat[g];
-    x.pf1 = __longlong_as_double(a.span[g]);
-  };
-
-  // Every event at or before `now` (prefill rounds, then decode rounds).
-  auto run_to = [&](double now) {
-    // one prefill round; false when no lane had an event
-    auto pre_round = [&]() -> bool {
-      bool fire[M];
-      uint64_t fm[M];
-      uint64_t any = 0;
-      double land[M], ftl[M], tcs[M];
-      int32_t fr[M], fd[M], fp[M], fo[M], foh[M];
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        const BInst& x = in[m];
-        double tc = kInf;
-        if (x.nact > 0) {
-          double rem = x.bw.k0 - x.v;
-          rem = rem < 0.0 ? 0.0 : rem;
-          tc = x.tl + rem * slowdown(beta, x.nact);
-        }
-        tcs[m] = tc;
-        fire[m] = isP && !dead && x.nact > 0 && tc <= now;
-        fm[m] = __ballot(fire[m]);
-        any |= fm[m];
-      });
-      if (any == 0) return false;
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        BInst& x = in[m];
-        const double tc = tcs[m];
-        land[m] = 0.0;
-        fr[m] = fd[m] = fp[m] = fo[m] = foh[m] = 0;
-        if (fire[m]) {
-          x.left = x.left - (double)x.nact * (x.bw.k0 - x.v);
-          x.v = x.bw.k0;
-          x.tl = tc;
-          tmax = fmax(tmax, tc);
-          const int64_t g = lo + x.bw.r0;
-          x.q -= 1;
-          x.kv = x.kv - (double)x.p0;
-          x.pend = x.pend - (double)x.p0;
-          a.ttft[g] = round_ns(tc - x.x0);
-          a.span[g] = __double_as_longlong(tc);
-          land[m] = tc + (double)x.p0 * xfer;
-          tmax = fmax(tmax, land[m]);
-          fr[m] = x.bw.r0;
-          fd[m] = x.dst0;
-          fp[m] = x.p0;
-          fo[m] = x.o0;
-          foh[m] = x.oh0;
-          x.head += 1;
-          x.nact -= 1;
-          if (x.nact == 0) {
-            x.left = 0.0;
-          } else {
-            window_pop(x.bw, rings[m], C, x.head, x.nact);
-            front_data(x);
-          }
-        }
-        ftl[m] = x.tl;
-      });
-      // the departing transfers go to their decode instances: every position
-      // (within the segments) that fired somewhere in the wave is read by
-      // every lane from its own segment, slot by slot
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        uint64_t rel = 0;
-#pragma unroll
-        for (int s0 = 0; s0 < 64; s0 += S) rel |= (S == 64) ? fm[m] : ((fm[m] >> s0) & ((1ull << (S & 63)) - 1ull));
-        while (rel) {
-          const int i = __ffsll((unsigned long long)rel) - 1;
-          rel &= rel - 1;
-          const int src = base + i;
-          const bool fi = __shfl((int)fire[m], src) != 0;
-          const int32_t di = __shfl(fd[m], src);
-          const double li = __shfl(land[m], src);
-          const double ti = __shfl(ftl[m], src);
-          const int32_t ri = __shfl(fr[m], src), pi = __shfl(fp[m], src), oi = __shfl(fo[m], src),
-                        ohi = __shfl(foh[m], src);
-          static_for<M>([&](auto nc) __attribute__((always_inline)) {
-            constexpr int mm = decltype(nc)::value;
-            BInst& y = in[mm];
-            if (isD && fi && di == j0 + mm) {
-              const int32_t at = ring_put(wrings[mm], C, y.wh, y.nw, li, ri, y.wtail, full);
-              if (at >= 0) {
-                window_put(y.tw, at, y.wh, li, ri);
-                if (at == y.wh) {
-                  y.pf1 = ti;
-                  y.p1 = pi;
-                  y.o1 = oi;
-                  y.oh1 = ohi;
-                }
-                y.nw += 1;
-              }
-            }
-          });
-        }
-      });
-      return true;
-    };
-    // two rounds per loop trip (measured: 8 % faster on a 4,096-replica cluster,
-    // 15 % on 65,536 replicas, than one)
-    while (pre_round() && pre_round()) {
-    }
-    // one decode round; false when no lane had an event
-    auto dec_round = [&]() -> bool {
-      bool anyf = false;
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        BInst& x = in[m];
-        double tc = kInf, tj = kInf;
-        if (x.nact > 0) {
-          double rem = x.bw.k0 - x.v;
-          rem = rem < 0.0 ? 0.0 : rem;
-          tc = x.tl + rem * slowdown(beta, x.nact);
-        }
-        if (x.nw > 0) tj = x.tw.k0;
-        const bool fire = isD && !dead && (x.nact > 0 || x.nw > 0) && (tc <= tj ? tc : tj) <= now;
-        anyf = anyf || fire;
-        if (!fire) return;
-        if (tc <= tj) {
-          x.left = x.left - (double)x.nact * (x.bw.k0 - x.v);
-          x.v = x.bw.k0;
-          x.tl = tc;
-          tmax = fmax(tmax, tc);
-          const int64_t g = lo + x.bw.r0;
-          x.q -= 1;
-          x.kv = x.kv - ((double)x.p0 + (double)x.o0);
-          x.pend = x.pend - (double)x.oh0;
-          a.span[g] = round_ns(tc - x.x0);
-          x.head += 1;
-          x.nact -= 1;
-          if (x.nact == 0) {
-            x.left = 0.0;
-          } else {
-            window_pop(x.bw, rings[m], C, x.head, x.nact);
-            front_data(x);
-          }
-        } else {
-          const int32_t r = x.tw.r0, pr = x.p1, orr = x.o1, ohr = x.oh1;
-          const double pfr = x.pf1;
-          x.wh += 1;
-          x.nw -= 1;
-          if (x.nw > 0) {
-            window_pop(x.tw, wrings[m], C, x.wh, x.nw);
-            transfer_data(x);
-          }
-          if (x.nact > 0) {
-            const double dv = (tj - x.tl) / slowdown(beta, x.nact);
-            x.v = x.v + dv;
-            x.left = x.left - (double)x.nact * dv;
-          }
-          x.tl = tj;
-          const double w = (double)(orr - 1) * dec_tok_ns;
-          x.owed = x.owed - w;
-          const double f = x.v + w;
-          const int32_t at = ring_put(rings[m], C, x.head, x.nact, f, r, x.btail, full);
-          if (at >= 0) {
-            window_put(x.bw, at, x.head, f, r);
-            if (at == x.head) {
-              x.x0 = pfr;
-              x.p0 = pr;
-              x.o0 = orr;
-              x.oh0 = ohr;
-            }
-            x.nact += 1;
-            x.left = x.left + w;
-          }
-        }
-      });
-      return __any(anyf);
-    };
-    while (dec_round()) {
-    }
-  };
-
-  auto fetch = [&](int32_t t) {
-    Req q0{0, 1, 1, 1, 0u, make_uint4(0u, 0u, 0u, 0u)};
-    if (t < len) {
-      const int64_t g = lo + t;
-      q0.arr = a.arrival[g];
-      q0.p = a.plen[g];
-      q0.o = a.olen[g];
-      q0.oh = a.ohat[g];
-      q0.c = a.cls[g];
-      if (samp) q0.ws = *reinterpret_cast<const uint4*>(a.samp + 4 * g);
-    }
-    return q0;
-  };
-
-  const int32_t Rmax = wave_max_nonneg((int32_t)len);
-  Req nx = fetch(0);
-  for (int32_t t = 0; t < Rmax; ++t) {
-    // request t, loaded a step ahead; request t + 1 is loaded now
-    const Req cur = nx;
-    nx = fetch(t + 1);
-    const int64_t arr = cur.arr;
-    const int32_t p = cur.p, o = cur.o, oh = cur.oh;
-    const uint32_t c = cur.c;
-    const uint4 ws = cur.ws;
-    const bool mine = t < len && !dead;
-    const int64_t g = lo + t;
-    const bool valid = mine && p >= 1 && o >= 1 && oh >= 1 && (int64_t)p + o <= INT32_MAX &&
-                       (int64_t)p + oh <= INT32_MAX && (int32_t)c < ncls && arr >= 0 && arr >= last;
-    if (mine && !valid) {
-      rej = true;
-      if (sl == 0) {
-        a.i_pre[g] = a.i_dec[g] = -1;
-        a.ttft[g] = a.span[g] = -1;
-      }
-    }
-    const double now = valid ? i64_to_f64(arr) : -1.0;
-    if (valid) {
-      last = arr;
-      tmax = fmax(tmax, now);
-    }
-    run_to(now);
-    // The rounds end on every lane at once, but the compiler may represent
-    // their loops with per-lane exits and reuse a lane-mask compare made
-    // inside them (where it has no bits for lanes it considers gone) after
-    // them; passing the counts through opaque() makes every later test of
-    // them a fresh compare.
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      in[m].nact = opaque(in[m].nact);
-      in[m].nw = opaque(in[m].nw);
-    }
-    // every instance's clock to the arrival
-    if (valid && (isP || isD)) {
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        BInst& x = in[m];
-        if (x.nact > 0) {
-          const double dv = (now - x.tl) / slowdown(beta, x.nact);
-          x.v = x.v + dv;
-          x.left = x.left - (double)x.nact * dv;
-        }
-        x.tl = now;
-      });
-    }
-    // each lane's key: the lowest of its instances' (lowest slot on equal
-    // keys; 0xffffffff: not offered)
-    uint32_t bkey = 0xffffffffu;
-    int32_t bm = 0;
-    if (valid && (isP || isD)) {
-      const int32_t n = isP ? P : D;
-      uint32_t c1 = 0, c2 = 0;
-      if (pol == kPolicyLearnedSampled) {
-        const uint32_t u = isP ? ws.x : ws.z, w2 = isP ? ws.y : ws.w;
-        c1 = __umulhi(u, (uint32_t)n);
-        const uint32_t x = __umulhi(w2, (uint32_t)(n - 1));
-        c2 = n > 1 ? x + (x >= c1 ? 1u : 0u) : c1;
-      }
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        const BInst& x = in[m];
-        const int32_t jj = j0 + m;
-        uint32_t key;
-        if (pol == kPolicyRoundRobin) {
-          key = jj == t % n ? 0u : 1u;
-        } else if (pol == kPolicyLeastLoaded) {
-          key = (uint32_t)x.q;
-        } else if (pol == kPolicyLengthThreshold) {
-          const bool part = isP || n == 1 || ((jj >= (n + 1) / 2) == (oh >= len_thr));
-          key = part ? (uint32_t)x.q : 0xffffffffu;
-        } else {
-          const float sg = sig[sblk * kMaxClasses + (int)(c & (kMaxClasses - 1))];
-          const float work = isP ? w_s * (float)p * tau_pre : w_s * (float)oh * tau_dec;
-          const double need = isP ? (double)p : (double)p + (double)oh;
-          float bl;
-          if (bmode == 0) {
-            double w = x.left < 0.0 ? 0.0 : x.left;
-            w = w + x.owed;
-            bl = (float)w * 1e-9f;
-          } else if (isP) {
-            bl = tau_pre * (float)x.pend + pre_base * (float)x.q;
-          } else {
-            bl = tau_dec * (float)x.pend;
-          }
-          const float press = (float)(x.kv + need) * inv;
-          const float load = w_b * bl * sg;
-          const float size = work * (1.0f + rho * press) * sg;
-          key = cost_key(load + size + w_q * (float)x.q);
-          if (pol == kPolicyLearnedSampled) key = ((uint32_t)jj == c1 || (uint32_t)jj == c2) ? key : 0xffffffffu;
-        }
-        key = ok[m] ? key : 0xffffffffu;
-        if (m == 0) {
-          bkey = key;
-        } else {
-          const bool lower = key < bkey;
-          bkey = lower ? key : bkey;
-          bm = lower ? m : bm;
-        }
-      });
-    }
-    uint32_t kp = isP ? bkey : 0xffffffffu, kd = isD ? bkey : 0xffffffffu;
-    const uint32_t kp0 = kp, kd0 = kd;
-    seg_min2<S>(kp, kd);
-    const int32_t wp = seg_first<S>(isP && kp0 == kp, lane);  // winning lanes
-    const int32_t wd = seg_first<S>(isD && kd0 == kd, lane);
-    int32_t mp = 0, md = 0;  // winning slots
-    if constexpr (M > 1) {
-      mp = (int32_t)seg_or<S>(sl == wp ? (uint32_t)bm : 0u);
-      md = (int32_t)seg_or<S>(sl == wd ? (uint32_t)bm : 0u);
-    }
-    const int32_t ip = wp * M + mp;
-    const int32_t id = (wd - LP) * M + md;
-    if (valid) {
-      if (sl == 0) {
-        a.i_pre[g] = ip;
-        a.i_dec[g] = id;
-      }
-      static_for<M>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        BInst& x = in[m];
-        if (isP && sl == wp && m == mp) {
-          const double w = pre_base_ns + (double)p * pre_tok_ns;
-          const double f = x.v + w;
-          const int32_t at = ring_put(rings[m], C, x.head, x.nact, f, t, x.btail, full);
-          if (at >= 0) {
-            window_put(x.bw, at, x.head, f, t);
-            if (at == x.head) {
-              x.x0 = now;
-              x.p0 = p;
-              x.o0 = o;
-              x.oh0 = oh;
-              x.dst0 = id;
-            }
-            x.nact += 1;
-            x.q += 1;
-            x.kv = x.kv + (double)p;
-            x.pend = x.pend + (double)p;
-            x.left = x.left + w;
-          }
-        }
-        if (isD && sl == wd && m == md) {
-          x.owed = x.owed + (double)(o - 1) * dec_tok_ns;
-          x.q += 1;
-          x.kv = x.kv + ((double)p + (double)o);
-          x.pend = x.pend + (double)oh;
-        }
-      });
-    }
-    // a replica whose ring overflowed stops (its outputs are not valid)
-    dead = seg_or<S>(full ? 1u : 0u) != 0;
-  }
-  run_to(kInf);
-  const uint32_t flag = (tmax >= kTimeLimit ? kFlagTimeRange : 0u) | (rej ? kFlagRejected : 0u) |
-                        (full ? kFlagBatchCap : 0u);
-  if (flag) atomicOr(a.flag, flag);
-}
-
 // ---------------------------------------------------------------------------
 // Wide variant: one replica per workgroup of W waves, M instances per lane in
-// registers as in the segment variant, for pools beyond its 128 instances.
+// registers, for pools beyond the 128 instances of lbat_kernel.
 // Instances are dealt to the waves round robin (instance j of a pool to wave
 // j mod W; in a wave the first lanes hold prefill instances and the next ones
 // decode instances).  A prefill instance evolves alone and a decode instance
@@ -1364,6 +916,11 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
 }
 
 }  // namespace bat
+}  // namespace rt
+
+#include "lbat_kernel.h"
+
+namespace rt {
 
 // One allocation, 256-byte aligned arrays: the ten state arrays, then the
 // two ring blocks.  With base == nullptr only the size is computed.
@@ -1410,21 +967,8 @@ static int32_t bat_lanes_per_wave(int64_t n_work) {
 
 hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, hipStream_t stream) {
   if (a.n_work <= 0) return hipSuccess;
-  const int64_t lanes = a.n_work * (int64_t)c.S;
-  const dim3 grid((unsigned)((lanes + bat::kBlock - 1) / bat::kBlock)), block(bat::kBlock);
-  // with at least two waves per SIMD to place, occupancy pays more than
-  // registers do; two instances per lane fit two waves per SIMD without
-  // spilling, three spill (measured on 16,384 replicas of 8 + 64 instances:
-  // two waves 27.5 ms, three 51.3 ms)
-  const bool many = lanes >= 2 * 64 * 1024;
-#define RT_BSEG_CASE(S_, M_)                                                              \
-  if (c.MP == M_ && c.S == S_) {                                                          \
-    if (many)                                                                             \
-      hipLaunchKernelGGL((bat::bseg_kernel<S_, M_ == 1 ? 3 : 2, M_>), grid, block, 0, stream, a, b);  \
-    else                                                                                  \
-      hipLaunchKernelGGL((bat::bseg_kernel<S_, 1, M_>), grid, block, 0, stream, a, b);    \
-    return hipGetLastError();                                                             \
-  }
+#define RT_BSEG_CASE(S_, M_) \
+  if (c.MP == M_ && c.S == S_) return bat::launch_lbat<S_, M_>(a, b, stream);
   RT_BSEG_FOR_EACH(RT_BSEG_CASE)
 #undef RT_BSEG_CASE
 #define RT_BWIDE_CASE(W_, M_)                                                                                      \
@@ -1441,7 +985,7 @@ hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, 
   const int32_t lpw = bat_lanes_per_wave(a.n_work);
   const int64_t waves = (a.n_work + lpw - 1) / lpw;
   const dim3 wgrid((unsigned)((waves * 64 + bat::kBlock - 1) / bat::kBlock));
-  hipLaunchKernelGGL(bat::bat_kernel, wgrid, block, 0, stream, a, b, lpw);
+  hipLaunchKernelGGL(bat::bat_kernel, wgrid, dim3(bat::kBlock), 0, stream, a, b, lpw);
   return hipGetLastError();
 }
 

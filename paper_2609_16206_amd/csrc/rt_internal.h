@@ -8,6 +8,7 @@
 namespace rt {
 
 constexpr int kMaxClasses = 8;
+constexpr int kComputeUnits = 256;  // of the GPU
 
 // One parameter point as the kernels read it: the public rt_point plus
 // host-computed constants (reciprocal cache capacities).
@@ -46,7 +47,7 @@ struct SimArgs {
   const DevPoint* points;
   const int32_t* work;  // replica ids of this launch, in processing order
   int64_t n_work;
-  int32_t max_inst;  // largest P + D among the launch's points (classes with the FIFOs in LDS)
+  int32_t max_inst;  // largest P + D among the launch's points (classes with queues in LDS)
   const int64_t* offsets;
   const int32_t* param_point;  // may be null: every replica uses point 0
   const int64_t* arrival;
@@ -88,7 +89,7 @@ constexpr int kDummyRecords = 1024;  // a power of two
 // per workgroup of S / 64 waves, instances dealt round-robin over the waves.
 // kLseg: one replica per aligned segment of S <= 64 lanes of one wave, a pool
 // on each half, one instance per lane, FIFOs in LDS.
-// kBat: the continuous-batching service model, one replica per lane.
+// kBat: the continuous-batching service model (shapes at RT_BSEG_FOR_EACH).
 enum SimKind { kSeg = 0, kWseg = 1, kBat = 2, kLseg = 3 };
 enum SimMode { kModeTrue = 0, kModeProxy = 1, kModeBase = 2, kModeTrueSampled = 3, kModeProxySampled = 4 };
 constexpr bool mode_ledger(int m) { return m == kModeProxy || m == kModeProxySampled; }  // proxy backlog

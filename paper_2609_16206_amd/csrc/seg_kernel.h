@@ -631,7 +631,6 @@ __global__ void __launch_bounds__(64 * kWaves) seg_kernel(SimArgs a) {
 // with few waves uses smaller workgroups, so that they spread over more
 // compute units (each unit's memory pipeline is shared by its waves).
 constexpr int kSegWaves = 4;
-constexpr int kComputeUnits = 256;
 
 template <int S, int M, int kMode>
 hipError_t launch_seg(const SimArgs& a, hipStream_t stream) {
