@@ -13,6 +13,8 @@
 // load of the pass issued before its first cost.  Rows of at most 64
 // instances laid out for 16-byte loads have a kernel of their own (16 lanes
 // per request, four consecutive instances per lane).  HBM-bound.
+#include <algorithm>
+
 #include "lane_ops.h"
 #include "rt_internal.h"
 
@@ -433,15 +435,26 @@ static hipError_t launch_rows(const ScoreArgs& a, hipStream_t stream) {
   }
 }
 
-// A shared snapshot takes a thread per kReq requests from this many requests
-// on: the thread walks the whole snapshot alone (about 45 ns an instance), and
-// fewer requests do not fill the GPU's SIMDs that way, while L lanes per
-// request cost about 0.7 ps a pair.
-constexpr int64_t kSharedMinReq = 1 << 16;
+// Lanes per request of the rows kernel: few instances per lane, and few idle
+// lanes.
+static int rows_lanes(int n) { return n <= 16 ? 4 : (n <= 64 ? 16 : 64); }
+
+// A shared snapshot takes a thread per kReq requests from a number of requests
+// on.  That thread walks the whole snapshot alone (30 to 40 ns an instance,
+// however few the requests are), while lanes per request cost about 0.7 ps per
+// place they have for an instance, idle ones and the last pass's included.
+// Lanes and thread: 65,000 requests x 66 instances 14.6 and 11.6 us, x 100 14.7
+// and 11.5, x 1,000 45.3 and 45.8; 48,000 x 300 20.7 and 16.6; 30,000 x 300 14.5
+// and 16.5.
+static bool thread_per_request(const ScoreArgs& a) {
+  const int64_t L = rows_lanes(a.n_inst), pass = L * std::min<int64_t>(4, (a.n_inst + L - 1) / L);
+  const int64_t places = (a.n_inst + pass - 1) / pass * pass;
+  return a.stride == 0 && (double)a.n_req * (double)places >= 55000.0 * (double)a.n_inst;
+}
 
 hipError_t launch_score(const ScoreArgs& a, hipStream_t stream) {
   if (a.n_req <= 0) return hipSuccess;
-  if (a.stride == 0 && a.n_req >= kSharedMinReq) {
+  if (thread_per_request(a)) {
     const int64_t per_block = (int64_t)kBlock * kReq;
     const int64_t blocks = (a.n_req + per_block - 1) / per_block;
     const size_t lds = sizeof(SnapEntry) * (((size_t)a.n_inst + 3) & ~(size_t)3);
@@ -455,10 +468,11 @@ hipError_t launch_score(const ScoreArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(score_rows16_kernel, dim3(blocks), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
   }
-  // lanes per request: few instances per lane, and few idle lanes
-  if (a.n_inst <= 16) return launch_rows<4>(a, stream);
-  if (a.n_inst <= 64) return launch_rows<16>(a, stream);
-  return launch_rows<64>(a, stream);
+  switch (rows_lanes(a.n_inst)) {
+    case 4: return launch_rows<4>(a, stream);
+    case 16: return launch_rows<16>(a, stream);
+    default: return launch_rows<64>(a, stream);
+  }
 }
 
 hipError_t launch_goodput(const GoodputArgs& a, hipStream_t stream) {
