@@ -148,8 +148,8 @@ struct LbatDims {
   static_assert(kCand0 % 16 == 0, "16-byte words");
 };
 
-template <int S, int M>
-__global__ void __launch_bounds__(64 * kLbatWaves, 2) lbat_kernel(SimArgs a, BatScratch b, LBat g) {
+template <int S, int M, int kOcc>
+__global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, BatScratch b, LBat g) {
   using Dm = LbatDims<S>;
   const int lane = (int)(threadIdx.x & 63);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -673,13 +673,13 @@ __global__ void __launch_bounds__(64 * kLbatWaves, 2) lbat_kernel(SimArgs a, Bat
   if (flag) atomicOr(a.flag, flag);
 }
 
-template <int S, int M>
-hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
+template <int S, int M, int kOcc>
+hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
   using Dm = LbatDims<S>;
   const int64_t waves = (a.n_work + Dm::kSegs - 1) / Dm::kSegs;
   const int64_t per_cu = (waves + kComputeUnits - 1) / kComputeUnits;
   const uint32_t wpb = (uint32_t)std::min<int64_t>(kLbatWaves, per_cu);
-  const uint32_t hold = (uint32_t)std::min<int64_t>(8, per_cu);  // waves a compute unit is to hold
+  const uint32_t hold = (uint32_t)std::min<int64_t>(4 * kOcc, per_cu);  // waves a compute unit is to hold
   LBat g{};
   g.max_inst = (uint32_t)a.max_inst;
   g.wave_bytes = (uint32_t)(Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0));
@@ -697,13 +697,31 @@ hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream
   g.rec_at = wpb * slots * g.stride;
   const uint32_t lds = g.rec_at + wpb * g.wave_bytes;
   if (lds > 64 * 1024) {  // (per device, so at every launch)
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lbat_kernel<S, M>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lbat_kernel<S, M, kOcc>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((lbat_kernel<S, M>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, stream, a,
+  hipLaunchKernelGGL((lbat_kernel<S, M, kOcc>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, stream, a,
                      b, g);
   return hipGetLastError();
+}
+
+// Three waves per SIMD where a launch has that many, two otherwise.  Segments of
+// 32 and 64 lanes gain from the third (with rings of at least two and one
+// entries): 16,384 replicas of 3 + 14
+// x 500 4.62 and 3.84 ms, 6,000 of 10 + 29 2.95 and 2.52.  Narrower ones have
+// more replicas, so more slots a wave, and their rings would be too short for
+// the batches of small pools: 65,536 of 1 + 2 x 1,000 8.4 ms with two waves and
+// 17.7 with three, of 2 + 6 13.1 and 20.9.  Two instances per lane spill.
+template <int S, int M>
+hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
+  if constexpr (M == 1 && S >= 32) {
+    using Dm = LbatDims<S>;
+    const int64_t waves = (a.n_work + Dm::kSegs - 1) / Dm::kSegs;
+    const int64_t bytes = (int64_t)Dm::kSegs * a.max_inst * 32 * (2 + 1 + 1) + Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0);
+    if (waves >= 12 * kComputeUnits && 12 * bytes <= kLdsBytes) return launch_lbat_occ<S, M, 3>(a, b, stream);
+  }
+  return launch_lbat_occ<S, M, 2>(a, b, stream);
 }
 
 }  // namespace bat

@@ -45,3 +45,13 @@ def test_many_waves(P, D, n):
     check_properties(pts, tr, gpu)
     assert np.array_equal(goodput_recount(pts, tr, gpu), met)
     follow_replicas(pts, tr, gpu, range(0, n, n // 40), gpu_goodput=g, gpu_met=met)
+
+
+@pytest.mark.parametrize("P,D,n", [(3, 14, 6200), (10, 29, 3100)])
+def test_three_waves_per_simd(P, D, n):
+    pts = _points(P, D)
+    tr = _bursts(pts, [20 - (i % 5) for i in range(n)], 10, 10**9)
+    gpu, g, met, flags = run_sim(pts, tr)
+    assert flags == 0
+    check_properties(pts, tr, gpu)
+    follow_replicas(pts, tr, gpu, range(0, n, n // 40), gpu_goodput=g, gpu_met=met)
