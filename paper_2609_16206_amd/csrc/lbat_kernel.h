@@ -22,7 +22,10 @@
 // instance, the request it was given last, which joins at its arrival with the
 // next iteration's events.  A round takes, on every lane and slot, a join that
 // comes before the next completion, then a completion that comes no later than
-// the next join; rounds go on while some lane had an event.
+// the next join; rounds go on while some lane had an event.  A prefill instance's
+// join comes before any completion: those up to its arrival were taken before it
+// was placed.  (The completion taken again from the clock at that arrival can
+// round to the arrival itself; the batch has the new member by then.)
 //
 // Queues.  The front entry is in registers, with all that the event needs; the
 // next ones are a sorted ring in LDS (32 bytes each; as many as the waves that
@@ -467,7 +470,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         constexpr int m = decltype(mc)::value;
         LInst& x = in[m];
         const double tj = x.j.fr.t;
-        const bool join = tj <= now && tj < x.tc;
+        const bool join = tj <= now && (isP || tj < x.tc);
         if (join) {
           Member e = x.j.fr;
           pop(x.j, jring[m], g.tmask, hj[m]);

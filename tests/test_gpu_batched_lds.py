@@ -1,7 +1,8 @@
 """Continuous batching in one wave: queues that outgrow their rings in LDS
 (sorted on into HBM and back), departures at once beyond a segment's list, a
 prefill so long that its decode placement is read back from the output, and
-launches of so many waves that a ring is a few entries."""
+launches of so many waves that a ring is a few entries; joins and completions
+at one instant."""
 import numpy as np
 import pytest
 
@@ -55,3 +56,54 @@ def test_three_waves_per_simd(P, D, n):
     assert flags == 0
     check_properties(pts, tr, gpu)
     follow_replicas(pts, tr, gpu, range(0, n, n // 40), gpu_goodput=g, gpu_met=met)
+
+
+# Traces on a grid of 1 ns (beta, first arrival, arrivals after it, prompts; one ns a token) in which a request
+# arrives just where a member's completion, taken again from the clock at that arrival, rounds to.  The request is
+# in the batch by then; were the member to leave first, a TTFT would differ by 1 ns.
+ROUNDED_TO_ARRIVAL = [
+    (0.25, 23925, [0, 0, 3, 7, 7, 11], [5, 3, 6, 4, 2, 2]),
+    (0.25, 16992, [0, 4, 7, 11, 12], [7, 5, 4, 3, 2]),
+    (0.25, 1863, [0, 3, 6, 6, 9, 13, 14, 18, 19], [2, 3, 4, 4, 4, 6, 2, 7, 5]),
+    (0.25, 24298, [0, 4, 7, 8, 11, 14, 15, 19, 23, 27, 27], [3, 3, 5, 4, 3, 5, 5, 5, 5, 4, 7]),
+    (0.5, 25912, [0, 0, 0, 2, 2, 5, 9, 10, 12], [1, 5, 3, 2, 5, 2, 4, 6, 2]),
+    (0.5, 25319, [0, 2, 2, 4, 7, 11, 12], [5, 7, 3, 7, 2, 5, 1]),
+]
+
+
+def _fine_points(shapes, betas):
+    return [dict(W.make_point(P, D, n_classes=1, policy="round_robin", service="batched"), batch_cap=1024, beta_pre=b,
+                 beta_dec=b, pre_base_ns=0, pre_tok_ns=1, dec_tok_ns=1, xfer_tok_ns=1) for P, D in shapes for b in betas]
+
+
+def _fine_trace(replicas, point_of):
+    """Replicas of (arrivals, prompts, outputs) as one trace."""
+    lens = [len(a) for a, _, _ in replicas]
+    tr = dict(arrival_ns=np.concatenate([a for a, _, _ in replicas]).astype(np.int64),
+              prompt_len=np.concatenate([p for _, p, _ in replicas]).astype(np.int32),
+              out_len=np.concatenate([o for _, _, o in replicas]).astype(np.int32))
+    tr["pred_out_len"] = tr["out_len"].copy()
+    tr["slo_class"] = np.zeros(len(tr["out_len"]), np.uint8)
+    tr["offsets"] = np.concatenate(([0], np.cumsum(lens))).astype(np.int64)
+    tr["param_point"] = np.asarray(point_of, np.int32)
+    return tr
+
+
+# Every segment width (so many replicas that the launch keeps it narrow), two instances a lane, one replica a workgroup.
+@pytest.mark.parametrize("D,n", [(1, 8400), (6, 4200), (14, 2100), (30, 1056), (60, 6), (126, 6), (140, 6)])
+def test_join_before_a_completion_that_rounds_to_its_arrival(D, n):
+    pts = _fine_points([(1, D)], [0.25, 0.5])
+    reps = [(t0 + np.array(a), p, np.ones(len(a))) for _, t0, a, p in ROUNDED_TO_ARRIVAL]
+    point_of = [0 if b == 0.25 else 1 for b, *_ in ROUNDED_TO_ARRIVAL]
+    tr = _fine_trace(reps * (n // 6), point_of * (n // 6))
+    assert _check(pts, tr, f"rounded to an arrival, 1+{D}") == 0
+
+
+def test_short_traces_on_a_fine_grid():
+    pts = _fine_points([(1, 1), (2, 2), (1, 6), (3, 1)], [0.25, 0.5, 1.0, 1.0 / 3.0])
+    rng = np.random.default_rng(17)
+    reps = []
+    for i in range(4000):
+        n = int(rng.integers(4, 32))
+        reps.append((rng.integers(0, 30_000) + np.cumsum(rng.integers(0, 5, n)), rng.integers(1, 8, n), rng.integers(1, 8, n)))
+    assert _check(pts, _fine_trace(reps, np.arange(4000) % len(pts)), "fine grid") == 0
