@@ -13,9 +13,11 @@
 // the admission.  A prefill that ends in iteration u (up to arrival u, so a
 // request before u, placed on its decode instance by the end of the iteration)
 // leaves a record in its segment's list in LDS; at the end of the iteration
-// the decode lanes take the transfers meant for them from the list, all of
-// which land after arrival u - 1.  A prefill lane that finds the list full
-// waits, and the iteration is repeated for its pool after the list was taken.
+// the decode lanes take the transfers meant for them from the list, none of
+// which lands before arrival u - 1.  A prefill lane that finds the list full
+// waits, and the iteration is repeated for its pool after the list was taken; the
+// wave's other lanes take no events meanwhile (a request without prefill work
+// would end in the iteration that placed it, before its decode placement).
 //
 // Events.  An instance has members (the batch, sorted by finish virtual time)
 // and joins to come: KV transfers sorted by landing time, or, on a prefill
@@ -553,7 +555,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         cur.r.now = -1.0;
         cur.r.p = 0;
       }
-      const double now = cur.r.now;
+      double now = cur.r.now;
       for (;;) {
         rounds(now, u);
         const bool held = isP && (stall & segm) != 0;
@@ -657,7 +659,10 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         }
         ndep = 0;
         if (__builtin_expect(stall == 0, 1)) break;
-        if (!held) cur.r.p = 0;  // placed already
+        if (!held) {  // placed already
+          cur.r.p = 0;
+          now = -1.0;
+        }
       }
       if (__builtin_expect(any_lane(full), 0)) dead = seg_or<S>(full ? 1u : 0u) != 0;  // (the replica stops)
       read_rec(cur, u + 1u - lag);

@@ -2,7 +2,8 @@
 (sorted on into HBM and back), departures at once beyond a segment's list, a
 prefill so long that its decode placement is read back from the output, and
 launches of so many waves that a ring is a few entries; joins and completions
-at one instant."""
+at one instant, and requests without prefill work next to replicas whose lists
+are full."""
 import numpy as np
 import pytest
 
@@ -107,3 +108,16 @@ def test_short_traces_on_a_fine_grid():
         n = int(rng.integers(4, 32))
         reps.append((rng.integers(0, 30_000) + np.cumsum(rng.integers(0, 5, n)), rng.integers(1, 8, n), rng.integers(1, 8, n)))
     assert _check(pts, _fine_trace(reps, np.arange(4000) % len(pts)), "fine grid") == 0
+
+
+@pytest.mark.parametrize("P,D,n_rep", [(5, 3, 4200), (9, 7, 2100), (20, 11, 1060), (40, 23, 20), (90, 37, 20)])
+def test_no_prefill_work_beside_full_lists(P, D, n_rep):
+    """Replicas whose prefill instances all end a request at one time, more at once than a segment lists, in waves
+    with replicas whose requests take no time to prefill."""
+    base = W.make_point(P, D, n_classes=1, policy="round_robin", service="batched", beta_pre=0.0)
+    pts = [dict(base, batch_cap=1024), dict(base, batch_cap=1024, pre_base_ns=0, pre_tok_ns=0, xfer_tok_ns=0)]
+    n = 6 * P + 3
+    burst = np.arange(n) // P * 10**10
+    reps = [(burst, np.full(n, 100), np.full(n, 20)), (np.arange(n) * 7_000_000, np.full(n, 100), np.full(n, 20))]
+    tr = _fine_trace(reps * (n_rep // 2), np.arange(n_rep) % 2)
+    assert _check(pts, tr, f"no prefill work {P}+{D}") == 0
