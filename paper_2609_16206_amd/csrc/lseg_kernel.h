@@ -112,8 +112,11 @@ struct LSlot {
 template <int S>
 constexpr int lreq_bytes() { return (64 / S) * (S * 2 * (int)sizeof(LReq) + 96); }
 constexpr bool mode_range(int m) { return mode_sampled(m) || m == kModeBase; }  // two more words per record and pool
+// (one pair more than the wave's records: each block's last step reads the
+// words of record S, its next, which are behind the last segment's)
+constexpr int kCandBytes = (64 + 1) * 2 * (int)sizeof(uint2);
 template <int S, int kMode>
-constexpr int lseg_fixed_lds() { return lreq_bytes<S>() + (mode_range(kMode) ? 64 * 2 * (int)sizeof(uint2) : 0); }
+constexpr int lseg_fixed_lds() { return lreq_bytes<S>() + (mode_range(kMode) ? kCandBytes : 0); }
 
 // The rings of a launch: every instance slot of a workgroup's waves has one
 // of mask / 16 + 1 entries, a power of two, at LDS address (slot * bytes);
@@ -325,8 +328,10 @@ __global__ void __launch_bounds__(64 * kSegWaves) lseg_kernel(SimArgs a, LRings 
     LReq r;
     uint2 c;
   };
-  // (record S of a block lies in the pad or in the next segment's records:
-  // read, not used)
+  // (record S of a block, and its candidates, lie in a pad or are the next
+  // segment's: read, not used)
+  static_assert((64 / S - 1) * (int)kSegRec + (S + 1) * 2 * (int)sizeof(LReq) <= lreq_bytes<S>(), "record S is in the wave's LDS");
+  static_assert((64 / S - 1) * S * 16 + (S + 1) * 16 <= kCandBytes, "and so are its candidates");
   auto read_rec = [&](Cur& q, uint32_t i) __attribute__((always_inline)) {
     const uint32_t at = my_rec + i * 2 * (uint32_t)sizeof(LReq);
     const u32x4 v[3] = {lds_get4(at), lds_get4(at + 16), lds_get4(at + 32)};
