@@ -704,9 +704,11 @@ hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t st
   g.stride = 32 * (kb + kt + 1);
   g.rec_at = wpb * slots * g.stride;
   const uint32_t lds = g.rec_at + wpb * g.wave_bytes;
-  if (lds > 64 * 1024) {  // (per device, so at every launch)
+  if (lds > 64 * 1024) {
+    // (per device, so at every launch; the whole of a compute unit's, so that
+    // a smaller launch of another thread takes nothing from this one)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lbat_kernel<S, M, kOcc>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((lbat_kernel<S, M, kOcc>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, stream, a,

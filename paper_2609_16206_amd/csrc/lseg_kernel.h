@@ -609,9 +609,11 @@ hipError_t launch_lseg(const SimArgs& a, hipStream_t stream) {
   g.mask = (1u << g.log_bytes) - kEntryBytes;
   g.rec_at = (uint32_t)wpb * slots << g.log_bytes;
   const uint32_t lds = g.rec_at + (uint32_t)wpb * kFixed;
-  if (lds > 64 * 1024) {  // (per device, so at every launch)
+  if (lds > 64 * 1024) {
+    // (per device, so at every launch; the whole of a compute unit's, so that
+    // a smaller launch of another thread takes nothing from this one)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lseg_kernel<S, kMode>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((lseg_kernel<S, kMode>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * (unsigned)wpb),

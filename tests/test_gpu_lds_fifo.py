@@ -2,10 +2,14 @@
 side) where its ring can go wrong: queues far beyond the ring that then drain
 many requests between two arrivals (refills one step ahead and at once), the
 edges of the segment widths, every scoring mode, few replicas (large rings)
-and many (small ones)."""
+and many (small ones); and launches of several threads."""
+import threading
+
 import numpy as np
 import pytest
+import torch
 
+from paper_2609_16206_amd import rt_router as R
 from paper_2609_16206_amd import workload as W
 from tests.gpu_common import log, run_sim
 from tests.parity import check_properties, follow_replicas, goodput_recount
@@ -47,3 +51,35 @@ def test_deep_rings_that_drain(P, D, n_rep, n_req):
     reps = range(n_rep) if n_rep < 100 else range(0, n_rep, 31)
     rep = follow_replicas(pts, tr, gpu, reps, gpu_goodput=g, gpu_met=met)
     log(f"LDS FIFOs {P}+{D}, {n_rep} x {n_req}: {rep}")
+
+
+@pytest.mark.parametrize("service,P,D", [("serial", 16, 16), ("batched", 40, 80)])
+def test_launches_of_two_threads_with_unequal_rings(service, P, D):
+    """Two host threads, each with a simulator and a stream of its own, launch the same kernel class with different
+    amounts of LDS: neither refuses the other's launch, and every call gives the first one's outputs."""
+    pt = W.make_point(P, D, n_classes=3, service=service)
+    failed = []
+
+    def work(n_rep):
+        try:
+            tr = R.to_device(W.make_trace(W.Workload("threads", 3, n_rep, 40, [pt], [W.mixed_bursty()])))
+            sim = R.Simulator([pt])
+            stream = torch.cuda.Stream()
+            first = None
+            for _ in range(60):
+                with torch.cuda.stream(stream):
+                    out = sim.run(tr, stream=stream)
+                stream.synchronize()
+                got = {k: v.cpu() for k, v in out.items()}
+                first = first or got
+                assert all(torch.equal(first[k], got[k]) for k in got)
+            sim.close()
+        except Exception as e:  # (an assertion in a thread is not the test's own)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(n,)) for n in (3, 300)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
