@@ -15,9 +15,10 @@
 // leaves a record in its segment's list in LDS; at the end of the iteration
 // the decode lanes take the transfers meant for them from the list, none of
 // which lands before arrival u - 1.  A prefill lane that finds the list full
-// waits, and the iteration is repeated for its pool after the list was taken; the
-// wave's other lanes take no events meanwhile (a request without prefill work
-// would end in the iteration that placed it, before its decode placement).
+// waits, and the iteration is repeated for its pool after the list was taken; in
+// the wave's other segments the request just placed does not join meanwhile (one
+// without prefill work would end in the iteration that placed it, before its
+// decode placement).
 //
 // Events.  An instance has members (the batch, sorted by finish virtual time)
 // and joins to come: KV transfers sorted by landing time, or, on a prefill
@@ -472,7 +473,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         constexpr int m = decltype(mc)::value;
         LInst& x = in[m];
         const double tj = x.j.fr.t;
-        const bool join = tj <= now && (isP || tj < x.tc);
+        const bool join = tj <= now && tj < x.tc;
         if (join) {
           Member e = x.j.fr;
           pop(x.j, jring[m], g.tmask, hj[m]);
@@ -555,7 +556,8 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         cur.r.now = -1.0;
         cur.r.p = 0;
       }
-      double now = cur.r.now;
+      const double now = cur.r.now;
+      bool again = false;
       for (;;) {
         rounds(now, u);
         const bool held = isP && (stall & segm) != 0;
@@ -642,6 +644,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
             if (isP) {
               x.j.fr = Member{now, (int32_t)u, p, now, o, oh};
               x.j.cnt = 1;
+              x.tc = kInf;  // (no completion before it joins)
             }
           });
           if (isD) *(lds_u16*)(uintptr_t)(tab0 + ((u - 1u) & (Dm::kTable - 1)) * 2u) = (uint16_t)(j0 + bm);
@@ -659,10 +662,20 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
         }
         ndep = 0;
         if (__builtin_expect(stall == 0, 1)) break;
-        if (!held) {  // placed already
-          cur.r.p = 0;
-          now = -1.0;
+        again = true;
+        if (!held) {
+          cur.r.p = 0;  // placed already; it joins with the next iteration
+          static_for<M>([&](auto mc) __attribute__((always_inline)) {
+            LInst& x = in[decltype(mc)::value];
+            if (isP && x.j.fr.t < kInf) x.tc = __builtin_nan("");
+          });
         }
+      }
+      if (__builtin_expect(again, 0)) {
+        static_for<M>([&](auto mc) __attribute__((always_inline)) {
+          LInst& x = in[decltype(mc)::value];
+          x.tc = x.tc != x.tc ? kInf : x.tc;
+        });
       }
       if (__builtin_expect(any_lane(full), 0)) dead = seg_or<S>(full ? 1u : 0u) != 0;  // (the replica stops)
       read_rec(cur, u + 1u - lag);
