@@ -610,18 +610,22 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
   __shared__ Depart dep[W][kDepart];
   __shared__ int32_t dep_n[W];           // entries of each wave's list; + kDepart + 1: more to come
   __shared__ unsigned long long best[2][2];  // per step parity and pool: (cost key << 32) | instance
-  __shared__ int32_t stop;               // a ring overflowed
+  __shared__ int32_t stop;               // a ring overflowed ...
+  __shared__ int32_t at_admission;       // ... when a request was placed
   __shared__ float sig[kMaxClasses];
   if (threadIdx.x < kMaxClasses) sig[threadIdx.x] = pt.sigma[threadIdx.x];
   if (threadIdx.x < 4) best[threadIdx.x >> 1][threadIdx.x & 1] = ~0ull;
-  if (threadIdx.x == 0) stop = 0;
+  if (threadIdx.x == 0) stop = at_admission = 0;
   __syncthreads();
 
   BInst in[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) init_binst(in[m]);
   double tmax = 0.0;
-  bool rej = false, full = false;
+  // a request was rejected: before the last placement, and after it (which does
+  // not count where the replica stopped at that placement)
+  bool rej = false, rej_new = false;
+  bool full = false;
   int64_t last = -1;
 
   auto next_done = [&](const BInst& x) __attribute__((always_inline)) {  // the batch's next completion
@@ -812,7 +816,7 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
     const bool valid = p >= 1 && o >= 1 && oh >= 1 && (int64_t)p + o <= INT32_MAX && (int64_t)p + oh <= INT32_MAX &&
                        (int32_t)c < ncls && arr >= 0 && arr >= last;
     if (__builtin_amdgcn_readfirstlane((int)valid) == 0) {  // (the same on every lane)
-      rej = true;
+      rej_new = true;
       if (threadIdx.x == 0) {
         a.i_pre[g] = a.i_dec[g] = -1;
         a.ttft[g] = a.span[g] = -1;
@@ -875,6 +879,10 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
     __syncthreads();
     const int32_t ip = (int32_t)(uint32_t)best[par][0], id = (int32_t)(uint32_t)best[par][1];
     dead = stop != 0;
+    if (!dead) {
+      rej = rej || rej_new;
+      rej_new = false;
+    }
     par ^= 1;
     static_for<M>([&](auto mc) __attribute__((always_inline)) {
       constexpr int m = decltype(mc)::value;
@@ -899,6 +907,8 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
           x.kv = x.kv + (double)p;
           x.pend = x.pend + (double)p;
           x.left = x.left + w;
+        } else {
+          at_admission = 1;
         }
       }
       if (isD && jj[m] == id) {
@@ -910,6 +920,8 @@ __global__ __launch_bounds__(64 * W) void bwide_kernel(SimArgs a, BatScratch b) 
     });
   }
   if (!dead) run_to(kInf);
+  __syncthreads();
+  rej = rej || (rej_new && at_admission == 0);
   const uint32_t flag = (tmax >= kTimeLimit ? kFlagTimeRange : 0u) | (rej ? kFlagRejected : 0u) |
                         (full ? kFlagBatchCap : 0u);
   if (flag) atomicOr(a.flag, flag);

@@ -93,6 +93,10 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) int32_t lds_i32;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 
+__device__ __forceinline__ void lds_min(uint32_t at, int32_t v) {
+  __hip_atomic_fetch_min((lds_i32*)(uintptr_t)at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 template <typename T>
 __device__ __forceinline__ T lds_get32(uint32_t at) {
   const u32x4 v[2] = {*(const lds_u32x4*)(uintptr_t)at, *(const lds_u32x4*)(uintptr_t)(at + 16)};
@@ -148,8 +152,10 @@ struct LbatDims {
   static constexpr int kRecBytes = kRecs * 32 + 32;       // and a gap, as above
   static constexpr int kList = S / 2 < 4 ? 4 : S / 2;     // departures listed at once
   static constexpr int kTable = kRecs < 32 ? 32 : kRecs;  // latest requests whose decode instance is at hand
+  static constexpr int kStop = kSegs < 2 ? 16 : kSegs * 8;  // where each replica first rejected a request and stopped
   static constexpr int kList0 = kSegs * kRecBytes, kDst0 = kList0 + kSegs * kList * 32,
-                       kTable0 = kDst0 + kSegs * kList * 4, kCand0 = kTable0 + kSegs * kTable * 2;
+                       kTable0 = kDst0 + kSegs * kList * 4, kStop0 = kTable0 + kSegs * kTable * 2,
+                       kCand0 = kStop0 + kStop;
   static constexpr int kCandBytes = kSegs * kRecs * 16;
   static_assert(kCand0 % 16 == 0, "16-byte words");
 };
@@ -202,6 +208,11 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
   const uint32_t list0 = w0 + Dm::kList0 + (uint32_t)(seg * Dm::kList * 32);
   const uint32_t dst0 = w0 + Dm::kDst0 + (uint32_t)(seg * Dm::kList * 4);
   const uint32_t tab0 = w0 + Dm::kTable0 + (uint32_t)(seg * Dm::kTable * 2);
+  // the segment's first request rejected, and the first that found a queue full:
+  // the replica stops there, and rejections after it do not count (in LDS:
+  // rarely written)
+  const uint32_t rej_at = w0 + Dm::kStop0 + (uint32_t)(seg * 8), full_at = rej_at + 4;
+  *(lds_i32*)(uintptr_t)rej_at = *(lds_i32*)(uintptr_t)full_at = INT32_MAX;
   const uint32_t cand0 = w0 + Dm::kCand0 + (uint32_t)(seg * Dm::kRecs * 16);
   // ring entries: never more than the queue's capacity leaves behind its front
   const int32_t limb = min((int32_t)(g.bmask >> 5) + 1, C - 1), limt = min((int32_t)(g.tmask >> 5) + 1, C - 1);
@@ -234,7 +245,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
     x.b = Queue{Member{kInf, 0, 0, 0.0, 0, 0}, 0, 0, 0, 0, 0u, 0.0, 0};
     x.j = x.b;
   }
-  bool rej = false, full = false, dead = false;
+  bool full = false, dead = false;
 
   auto any_lane = [](bool c) __attribute__((always_inline)) { return __builtin_amdgcn_ballot_w64(c) != 0; };
   auto before = [](double t, int32_t r, double t2, int32_t r2) __attribute__((always_inline)) {
@@ -246,8 +257,9 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
     if (isD) a.span[lo + r] = __double_as_longlong(x0);
   };
 
-  // e into a queue (on the active lanes).
-  auto insert = [&](Queue& Q, uint32_t ring, uint32_t mask, int32_t lim, Entry* hbm, const Member& e)
+  // e into a queue (on the active lanes), on the way to the placement of request
+  // `step`.
+  auto insert = [&](Queue& Q, uint32_t ring, uint32_t mask, int32_t lim, Entry* hbm, const Member& e, int32_t step)
                     __attribute__((always_inline)) {
     if (__builtin_expect(!any_lane(Q.cnt > 0), 1)) {  // alone in it
       Q.fr = e;
@@ -260,6 +272,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
       if (Q.n >= lim) {
         if (Q.cnt >= C) {
           full = true;
+          lds_min(full_at, step);
           put = false;
         } else if (!before(e.t, e.r, Q.tt, Q.tr)) {  // behind the LDS ring
           int32_t i = Q.hx + Q.x;
@@ -445,7 +458,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
       *(lds_u32x4*)(uintptr_t)(cand0 + (i & (Dm::kRecs - 1)) * 16u) = u32x4{c1, c2, d1, d2};
     }
     if (inside && !acc) {
-      rej = true;
+      lds_min(rej_at, (int32_t)i);
       a.ttft[lo + i] = a.span[lo + i] = -1;
     }
   };
@@ -482,7 +495,8 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
           x.owed = x.owed - w;
           x.left = x.left + w;
           e.t = x.v + w;
-          insert(x.b, bring[m], g.bmask, limb, hb[m], e);
+          // (a prefill instance took the request when it was placed)
+          insert(x.b, bring[m], g.bmask, limb, hb[m], e, isP ? e.r : (int32_t)(u - 1u));
           x.d0 = x.b.fr.r == e.r ? -1 : x.d0;
           resize(x, 1.0);
         }
@@ -657,7 +671,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
           const bool mine = isD && i < ndep;
           static_for<M>([&](auto mc) __attribute__((always_inline)) {
             constexpr int m = decltype(mc)::value;
-            if (mine && d == j0 + m) insert(in[m].j, jring[m], g.tmask, limt, hj[m], e);
+            if (mine && d == j0 + m) insert(in[m].j, jring[m], g.tmask, limt, hj[m], e, (int32_t)u);
           });
         }
         ndep = 0;
@@ -690,6 +704,7 @@ __global__ void __launch_bounds__(64 * kLbatWaves, kOcc) lbat_kernel(SimArgs a, 
 #pragma unroll
   for (int m = 0; m < M; ++m)
     late = late || (ok[m] && (in[m].tl >= kTimeLimit || (!dead && in[m].b.cnt + in[m].j.cnt > 0)));
+  const bool rej = *(const lds_i32*)(uintptr_t)rej_at < *(const lds_i32*)(uintptr_t)full_at;
   const uint32_t flag = (late ? kFlagTimeRange : 0u) | (rej ? kFlagRejected : 0u) | (full ? kFlagBatchCap : 0u);
   if (flag) atomicOr(a.flag, flag);
 }

@@ -3,7 +3,7 @@
 prefill so long that its decode placement is read back from the output, and
 launches of so many waves that a ring is a few entries; joins and completions
 at one instant, and requests without prefill work next to replicas whose lists
-are full."""
+are full; and rejections around the request that finds a queue full."""
 import numpy as np
 import pytest
 
@@ -121,3 +121,26 @@ def test_no_prefill_work_beside_full_lists(P, D, n_rep):
     reps = [(burst, np.full(n, 100), np.full(n, 20)), (np.arange(n) * 7_000_000, np.full(n, 100), np.full(n, 20))]
     tr = _fine_trace(reps * (n_rep // 2), np.arange(n_rep) % 2)
     assert _check(pts, tr, f"no prefill work {P}+{D}") == 0
+
+
+@pytest.mark.parametrize("late", [False, True])
+@pytest.mark.parametrize("where", ["prefill", "transfers", "decode"])
+@pytest.mark.parametrize("width", [1, 40, 100, 200, 1024])  # the instances on the side that does not overflow
+def test_rejections_around_a_full_queue(width, where, late):
+    """A replica stops at the request that finds a queue full: requests after it are not looked at, so a bad one
+    among them sets no flag; one before it does."""
+    P, D = (1, width) if where == "prefill" else (width, 1)
+    pt = dict(W.make_point(P, D, n_classes=1, policy="round_robin", service="batched"), batch_cap=2)
+    n = 8
+    gap = 0 if where == "prefill" else 10**12
+    if where == "transfers":
+        pt.update(xfer_tok_ns=1 << 40)
+    elif where == "decode":
+        pt.update(xfer_tok_ns=0, dec_tok_ns=1 << 40)
+    # the third request (transfer, decode member) is one too many: found at its own admission, or by the arrival after
+    stop = 2 if where == "prefill" else 3
+    bad = stop + 1 if late else stop - 1
+    tr = _fine_trace([(np.arange(n) * gap, np.full(n, 100), np.full(n, 20))], [0])
+    tr["prompt_len"][bad] = 0
+    flags = run_sim([pt], tr)[3]
+    assert flags & ~4 == (8 if late else 9)
