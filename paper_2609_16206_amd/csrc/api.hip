@@ -573,6 +573,7 @@ static rt::SimArgs sim_args(const rt_sim* sim, const rt_trace* trace, const rt_s
   a.work = nullptr;
   a.n_work = 0;
   a.max_inst = 0;
+  a.call_waves = 0;
   // record planes by record size: index 0 of each pool's plane
   for (int k = 0; k < 2; ++k) planes[0][k] = planes[1][k] = nullptr;
   for (int k = 0; k < 2 && sc && L.any_serial; ++k) {
@@ -586,12 +587,16 @@ static rt::SimArgs sim_args(const rt_sim* sim, const rt_trace* trace, const rt_s
   return a;
 }
 
-// Launches class c of the plan over its replicas (work list at d_work).
-static hipError_t launch_class(int c, rt::SimArgs a, const PlanBufs& b, const int32_t* d_work, char* (&planes)[2][2],
-                               const rt::BatScratch* bs, hipStream_t where) {
+// Launches class c of the plan over its replicas (work list at d_work), beside the
+// plan's other classes or alone.
+static hipError_t launch_class(int c, rt::SimArgs a, const PlanBufs& b, bool beside, const int32_t* d_work,
+                               char* (&planes)[2][2], const rt::BatScratch* bs, hipStream_t where) {
   a.work = d_work + b.start[c];
   a.n_work = b.count[c];
   a.max_inst = b.max_inst[c];
+  a.call_waves = 0;
+  for (int k = 0; k < b.n_act; ++k)
+    if (beside || b.act[k] == c) a.call_waves += (b.count[b.act[k]] * rt::sim_class(b.act[k]).S + 63) / 64;
   const int lg = rt::mode_ledger(rt::sim_class(c).mode) ? 1 : 0;
   a.rec[0] = planes[lg][0];
   a.rec[1] = planes[lg][1];
@@ -744,7 +749,7 @@ rt_status rt_sim_run_replicas(rt_sim* sim, const rt_trace* trace, rt_sim_out* ou
       where = sim->lanes[k];
       if ((e = hipStreamWaitEvent(where, sim->fork, 0)) != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
     }
-    if ((e = launch_class(b.act[k], a, b, sim->d_work, planes, bs.data(), where)) != hipSuccess)
+    if ((e = launch_class(b.act[k], a, b, true, sim->d_work, planes, bs.data(), where)) != hipSuccess)
       return hip_fail(e, "launch(sim)");
     if (nact > 1 && (e = hipEventRecord(sim->joins[k], where)) != hipSuccess) return hip_fail(e, "hipEventRecord");
   }
@@ -837,7 +842,7 @@ rt_status rt_sim_run_replicas_noalloc(rt_sim* sim, const rt_trace* trace, rt_sim
   }
   // every class on the caller's stream, dearest first (no internal streams)
   for (int k = 0; k < b.n_act; ++k)
-    if ((e = launch_class(b.act[k], a, b, d_work, planes, nullptr, stream)) != hipSuccess)
+    if ((e = launch_class(b.act[k], a, b, false, d_work, planes, nullptr, stream)) != hipSuccess)
       return hip_fail(e, "launch(sim)");
   if (sim->timing) {
     if ((e = hipEventRecord(sim->t1, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");

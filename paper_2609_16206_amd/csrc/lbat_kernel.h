@@ -63,7 +63,6 @@
 namespace rt {
 namespace bat {
 
-constexpr int kLdsBytes = 160 * 1024;
 constexpr int kLbatWaves = 4;  // waves of a workgroup, at most
 
 // A member of a batch, or a join to come.
@@ -713,14 +712,13 @@ template <int S, int M, int kOcc>
 hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
   using Dm = LbatDims<S>;
   const int64_t waves = (a.n_work + Dm::kSegs - 1) / Dm::kSegs;
-  const int64_t per_cu = (waves + kComputeUnits - 1) / kComputeUnits;
-  const uint32_t wpb = (uint32_t)std::min<int64_t>(kLbatWaves, per_cu);
-  const uint32_t hold = (uint32_t)std::min<int64_t>(4 * kOcc, per_cu);  // waves a compute unit is to hold
+  const LdsShare share = lds_share(a.call_waves, 4 * kOcc);
+  const uint32_t wpb = share.wpb;
   LBat g{};
   g.max_inst = (uint32_t)a.max_inst;
   g.wave_bytes = (uint32_t)(Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0));
   const uint32_t slots = (uint32_t)Dm::kSegs * g.max_inst;  // of a wave
-  const uint32_t room = kLdsBytes / hold - g.wave_bytes;
+  const uint32_t room = share.bytes - g.wave_bytes;
   // entries of the two rings: what the compute unit's waves leave each slot
   uint32_t kb = 16, kt = 8;
   while (kb > 1 && slots * 32u * (kb + kt + 1) > room) {
@@ -736,7 +734,7 @@ hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t st
     // (per device, so at every launch; the whole of a compute unit's, so that
     // a smaller launch of another thread takes nothing from this one)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lbat_kernel<S, M, kOcc>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((lbat_kernel<S, M, kOcc>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, stream, a,
@@ -744,20 +742,22 @@ hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t st
   return hipGetLastError();
 }
 
-// Three waves per SIMD where a launch has that many, two otherwise.  Segments of
-// 32 and 64 lanes gain from the third (with rings of at least two and one
-// entries): 16,384 replicas of 3 + 14
-// x 500 4.62 and 3.84 ms, 6,000 of 10 + 29 2.95 and 2.52.  Narrower ones have
-// more replicas, so more slots a wave, and their rings would be too short for
-// the batches of small pools: 65,536 of 1 + 2 x 1,000 8.4 ms with two waves and
-// 17.7 with three, of 2 + 6 13.1 and 20.9.  Two instances per lane spill.
+// Three waves per SIMD where a call has more than two, two otherwise.  Segments
+// of 32 and 64 lanes gain from the third (with rings of at least two and one
+// entries): 16,384 replicas of 3 + 14 x 500 4.62 and 3.84 ms, 5,120 x 400 1.54
+// and 1.16, 2,560 of 10 + 29 x 300 0.98 and 0.75.  Narrower ones have more
+// replicas, so more slots a wave, and their rings would be too short for the
+// batches of small pools: 65,536 of 1 + 2 x 1,000 8.4 ms with two waves and 17.7
+// with three, of 2 + 6 13.1 and 20.9.  With three, segments of 32 lanes spill 36
+// registers a lane and those of 64 two (the figures have that in them); two
+// instances per lane fill the registers of two waves.
 template <int S, int M>
 hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
   if constexpr (M == 1 && S >= 32) {
     using Dm = LbatDims<S>;
-    const int64_t waves = (a.n_work + Dm::kSegs - 1) / Dm::kSegs;
-    const int64_t bytes = (int64_t)Dm::kSegs * a.max_inst * 32 * (2 + 1 + 1) + Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0);
-    if (waves >= 12 * kComputeUnits && 12 * bytes <= kLdsBytes) return launch_lbat_occ<S, M, 3>(a, b, stream);
+    const uint32_t bytes = (uint32_t)Dm::kSegs * (uint32_t)a.max_inst * 32 * (2 + 1 + 1) + Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0);
+    if (waves_per_cu(a.call_waves) > 8 && bytes <= lds_share(a.call_waves, 12).bytes)
+      return launch_lbat_occ<S, M, 3>(a, b, stream);
   }
   return launch_lbat_occ<S, M, 2>(a, b, stream);
 }

@@ -68,8 +68,6 @@
 namespace rt {
 namespace seg {
 
-constexpr int kLdsPerCu = 160 * 1024;
-
 // A request as one pool's lanes read it.
 struct alignas(16) LReq {
   double now;      // arrival (ns) if the request is accepted, else -1
@@ -591,24 +589,46 @@ __global__ void __launch_bounds__(64 * kSegWaves) lseg_kernel(SimArgs a, LRings 
   if (flag) atomicOr(a.flag, flag);
 }
 
+// Rings of a wave with `bytes` of LDS, `fixed` of them for its records, over
+// `slots` instances: log2 of a ring's bytes, a power of two (4 to 256 entries).
+inline uint32_t ring_log_bytes(uint32_t bytes, uint32_t fixed, uint32_t slots) {
+  uint32_t lg = 6;
+  while (lg < 12 && (slots << (lg + 1)) <= bytes - fixed) ++lg;
+  return lg;
+}
+
+// A compute unit holds two waves per SIMD of a launch that has so many, and a
+// third, in segments of 16 lanes and more, where that costs the rings no more
+// than half their entries and leaves eight, and where it does not only move the
+// last pass over the GPU (13 to 16 waves a compute unit: two passes of eight).
+// 9,000 replicas of 2 + 6 x 1,000: 1.10 ms with two, 0.95 with three; 14,336:
+// 1.30 and 1.34; 24,576: 1.94 and 1.80; 32,768 of 4 + 8 x 300 (eight entries)
+// 0.71 and 0.66, least loaded (four) 0.48 and 0.72.  Segments of 8 lanes: 65,536
+// of 1 + 3 x 300 0.99 and 1.12.
+template <int S>
+int64_t lseg_most_waves(int64_t call_waves, uint32_t fixed, uint32_t slots) {
+  if (S < 16) return 8;
+  const int64_t per_cu = waves_per_cu(call_waves);
+  if (per_cu <= 8 || (per_cu > 12 && per_cu <= 16)) return 8;
+  const uint32_t two = ring_log_bytes(lds_share(call_waves, 8).bytes, fixed, slots);
+  const uint32_t three = ring_log_bytes(lds_share(call_waves, 12).bytes, fixed, slots);
+  return three >= 7 && three + 1 >= two ? 12 : 8;
+}
+
 template <int S, int kMode>
 hipError_t launch_lseg(const SimArgs& a, hipStream_t stream) {
   constexpr int64_t kSegs = 64 / S;
   constexpr uint32_t kFixed = (uint32_t)lseg_fixed_lds<S, kMode>();
   const int64_t waves = (a.n_work + kSegs - 1) / kSegs;
-  const int64_t per_cu = (waves + kComputeUnits - 1) / kComputeUnits;
-  const int64_t wpb = std::min<int64_t>(kSegWaves, std::max<int64_t>(1, per_cu));
-  // ring size: what the waves that a compute unit is to hold leave each slot
-  const uint32_t hold = (uint32_t)std::min<int64_t>(8, std::max<int64_t>(per_cu, 1));
   const uint32_t slots = (uint32_t)(kSegs * a.max_inst);  // of a wave
-  const uint32_t room = kLdsPerCu / hold - kFixed;
+  const LdsShare share = lds_share(a.call_waves, lseg_most_waves<S>(a.call_waves, kFixed, slots));
+  const uint32_t wpb = share.wpb;
   LRings g{};
   g.max_inst = (uint32_t)a.max_inst;
-  g.log_bytes = 6;
-  while (g.log_bytes < 12 && (slots << (g.log_bytes + 1)) <= room) ++g.log_bytes;
+  g.log_bytes = ring_log_bytes(share.bytes, kFixed, slots);
   g.mask = (1u << g.log_bytes) - kEntryBytes;
-  g.rec_at = (uint32_t)wpb * slots << g.log_bytes;
-  const uint32_t lds = g.rec_at + (uint32_t)wpb * kFixed;
+  g.rec_at = wpb * slots << g.log_bytes;
+  const uint32_t lds = g.rec_at + wpb * kFixed;
   if (lds > 64 * 1024) {
     // (per device, so at every launch; the whole of a compute unit's, so that
     // a smaller launch of another thread takes nothing from this one)
@@ -616,8 +636,8 @@ hipError_t launch_lseg(const SimArgs& a, hipStream_t stream) {
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((lseg_kernel<S, kMode>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * (unsigned)wpb),
-                     lds, stream, a, g);
+  hipLaunchKernelGGL((lseg_kernel<S, kMode>), dim3((unsigned)((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds,
+                     stream, a, g);
   return hipGetLastError();
 }
 

@@ -9,6 +9,8 @@ namespace rt {
 
 constexpr int kMaxClasses = 8;
 constexpr int kComputeUnits = 256;  // of the GPU
+constexpr int kLdsPerCu = 160 * 1024;
+constexpr int kLdsGranule = 1280;  // LDS is granted to a workgroup in these
 
 // One parameter point as the kernels read it: the public rt_point plus
 // host-computed constants (reciprocal cache capacities).
@@ -48,6 +50,7 @@ struct SimArgs {
   const int32_t* work;  // replica ids of this launch, in processing order
   int64_t n_work;
   int32_t max_inst;  // largest P + D among the launch's points (classes with queues in LDS)
+  int64_t call_waves;  // waves of this launch and of those that run beside it
   const int64_t* offsets;
   const int32_t* param_point;  // may be null: every replica uses point 0
   const int64_t* arrival;
@@ -132,6 +135,33 @@ BatScratch bat_scratch_carve(char* base, int64_t S, int32_t NI, int32_t C);
 // P + D).
 #define RT_BSEG_FOR_EACH(X) X(4, 1) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2)
 #define RT_BWIDE_FOR_EACH(X) X(4, 1) X(8, 1) X(8, 2) X(8, 3)
+// LDS of the one-wave kernels with rings in it: a workgroup is up to four waves,
+// one on each SIMD, and a compute unit is to hold its share of the call's waves
+// (those of every class that runs beside this one), but `most` waves at most.
+// LDS is granted by workgroup, so a wave's share is a quarter of what a
+// workgroup may take.  (With a share per wave instead, 5 to 7 waves a compute
+// unit left room for one workgroup of four, and the launch took two passes:
+// 4,600 serial replicas of 2 + 6 x 1,000 0.91 ms, 0.67 ms so; 1,100 batched of
+// 8 + 64 x 300 1.38 and 0.79 ms.  Workgroups of one wave take 0.60 ms in the
+// first case, but leave SIMDs unevenly filled in full launches and in calls of
+// several classes: 16,384 of 2 + 6 1.56 ms against 1.33, a seven-policy study of
+// 2,000 replicas 1.07 against 0.90.)
+struct LdsShare {
+  int64_t hold;    // waves that a compute unit is to hold
+  uint32_t wpb;    // waves of a workgroup
+  uint32_t bytes;  // of a wave
+};
+inline int64_t waves_per_cu(int64_t waves) { return waves <= kComputeUnits ? 1 : (waves + kComputeUnits - 1) / kComputeUnits; }
+inline LdsShare lds_share(int64_t call_waves, int64_t most) {
+  LdsShare s{};
+  const int64_t per_cu = waves_per_cu(call_waves);
+  s.hold = per_cu < most ? per_cu : most;
+  s.wpb = s.hold < 4 ? (uint32_t)s.hold : 4u;
+  const int64_t groups = (s.hold + s.wpb - 1) / s.wpb;
+  s.bytes = (uint32_t)(kLdsPerCu / groups / kLdsGranule * kLdsGranule) / s.wpb & ~15u;
+  return s;
+}
+
 hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, hipStream_t stream);
 int64_t bat_lanes(const SimClass& c, int64_t n_work);
 

@@ -144,3 +144,15 @@ def test_rejections_around_a_full_queue(width, where, late):
     tr["prompt_len"][bad] = 0
     flags = run_sim([pt], tr)[3]
     assert flags & ~4 == (8 if late else 9)
+
+
+# 5 to 7 and 9 to 11 waves a compute unit (and a ragged last workgroup).
+@pytest.mark.parametrize("P,D,n", [(2, 6, 4610), (2, 6, 8300), (1, 2, 17100), (3, 14, 2500), (3, 14, 4200), (12, 20, 4600),
+                                   (10, 29, 1300), (10, 29, 2070), (8, 64, 1100)])
+def test_waves_between_whole_workgroups(P, D, n):
+    pts = _points(P, D)
+    tr = _bursts(pts, [20 - (i % 5) for i in range(n)], 10, 10**9)
+    gpu, g, met, flags = run_sim(pts, tr)
+    assert flags == 0
+    check_properties(pts, tr, gpu)
+    follow_replicas(pts, tr, gpu, range(0, n, n // 60), gpu_goodput=g, gpu_met=met)

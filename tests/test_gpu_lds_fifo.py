@@ -53,6 +53,38 @@ def test_deep_rings_that_drain(P, D, n_rep, n_req):
     log(f"LDS FIFOs {P}+{D}, {n_rep} x {n_req}: {rep}")
 
 
+# Launch sizes on both sides of each line at which a pool changes its kernel, its ring length or the workgroups that
+# share a compute unit: a ragged last workgroup, 5 to 7, 9 to 12 and 13 to 16 waves a compute unit, segments of four
+# lanes.
+@pytest.mark.parametrize("P,D,n_rep", [(2, 6, 4610), (2, 6, 9001), (2, 6, 13001), (2, 6, 17003), (3, 3, 9002), (4, 1, 6200),
+                                       (8, 1, 4107), (9, 1, 1601), (8, 8, 5003), (8, 8, 9005), (5, 5, 9001), (8, 2, 33001),
+                                       (2, 12, 33001), (16, 16, 3001), (24, 3, 1030), (32, 32, 601), (2, 32, 1501)])
+def test_launch_sizes(P, D, n_rep):
+    pts = [W.make_point(P, D, n_classes=3, policy=pol, backlog_mode=bm, kv_cap=20_000, len_threshold=150)
+           for pol, bm in MODES]
+    # (one mode a call, so that the call has the launch size of that mode's class; every replica one of 32 traces)
+    traf = W.mixed_bursty()
+    traf = traf.scaled(1.2 * W.capacity_rps(pts[0], traf) / traf.mean_rate())
+    parts = [W.replica_arrays(61, i, traf, 70 - i % 5) for i in range(32)]
+    for pt in pts:
+        rep = [parts[i % 32] for i in range(n_rep)]
+        tr = {key: np.concatenate([q[key] for q in rep]) for key in parts[0]}
+        lens = [70 - (i % 32) % 5 for i in range(n_rep)]
+        tr["offsets"] = np.concatenate(([0], np.cumsum(lens))).astype(np.int64)
+        tr["param_point"] = np.zeros(n_rep, np.int32)
+        if pt["policy"] == "learned_sampled":
+            W.add_sample_words(tr, 11)
+        gpu, g, met, flags = run_sim([pt], tr)
+        assert flags == 0
+        check_properties([pt], tr, gpu)
+        follow_replicas([pt], tr, gpu, range(0, n_rep, n_rep // 60), gpu_goodput=g, gpu_met=met)
+        if pt["policy"] != "learned_sampled":  # replicas of one trace are alike, in whichever wave
+            k = sum(lens[:32])
+            for key in gpu:
+                whole = gpu[key][: len(gpu[key]) // k * k].reshape(-1, k)
+                assert (whole == whole[0]).all(), key
+
+
 @pytest.mark.parametrize("service,P,D", [("serial", 16, 16), ("batched", 40, 80)])
 def test_launches_of_two_threads_with_unequal_rings(service, P, D):
     """Two host threads, each with a simulator and a stream of its own, launch the same kernel class with different
