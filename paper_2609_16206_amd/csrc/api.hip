@@ -46,7 +46,6 @@ bool finite_nonneg(float x) { return std::isfinite(x) && x >= 0.0f; }
 constexpr int64_t kMaxNs = int64_t(1) << 40;
 constexpr int32_t kMaxBatchCap = 65536;
 constexpr int32_t kDefaultBatchCap = 256;
-constexpr int kSmallPool = 8;     // see plan_launch
 constexpr int kSimds = 256 * 4;  // MI355X: 256 compute units x 4 SIMDs
 
 // Limits of rt_sim_run_replicas_noalloc: the device scratch each GPU holds
@@ -233,18 +232,64 @@ struct PlanBufs {
   int n_act;
 };
 
-// Plan.  Each point runs one kernel class.
+// Does a point run the one-wave kernel with its FIFOs in LDS (kLseg) in a call of
+// `per_cu` waves of such segments a compute unit?  `many`: the call has two waves
+// per SIMD of segments just wide enough (see plan_launch).
 //
-// Pools of at most kSmallPool instances a side always take the class with the
-// FIFOs in LDS (kLseg).  For the others the launch's size decides, counted in
-// waves of segments just wide enough for one instance per lane: with fewer than two
-// per SIMD every replica is a latency chain and takes the class with the
-// shortest step (kLseg while its waves are that few too: its halves make it up
-// to twice as wide); with more, the GPU's issue rate is the limit and each point
-// takes the segment class with the fewest issue slots per replica-step (lanes x
-// step cost).  Measured, ns per request of many replicas, ledger backlog: 2 + 3
-// instances kLseg 0.073, the best of kSeg 0.135; 2 + 6 0.097 and 0.102; 2 + 8
-// 0.099 and 0.111; 2 + 16 0.172 and 0.122; 2 + 32 0.31 and 0.21.
+// That kernel has the shorter step, but its halves make it up to twice as wide,
+// and a queue beyond its ring costs more than one of kSeg's.  Rings are long (64
+// entries and more) where a compute unit has few waves; queues are where few
+// decode instances serve many prefill instances.  Measured, ms with kSeg and
+// kLseg, loads of 0.8 and 1.2, clock backlog where nothing else is said:
+//   - up to two waves a compute unit, any shape: kLseg 1.2 to 1.9 times as fast;
+//   - one decode instance and eight or more prefill: up to three, 4,096 of 8 + 1 x
+//     800 0.64 and 0.75, 1,500 of 9 + 1 0.59 and 0.45;
+//   - at most four instances a side: at any size, 65,536 of 3 + 3 x 300 2.36 and 1.02
+//     (of 4 + 1, whose queues are the longest, 40,000 x 200 1.08 and 0.75, but
+//     overloaded 8,192 x 500 0.53 and 0.57);
+//   - five to eight a side, more of them decode instances: 65,536 of 2 + 6 x 300
+//     1.59 and 1.27, of 4 + 8 1.46 and 1.28.  Pools of up to eight instances in all
+//     between 12 and 16 waves a compute unit excepted: kSeg holds twice the
+//     replicas a wave, so all in one pass (14,336 of 2 + 6 x 1,000 1.17 and 1.30);
+//   - as many prefill instances or more: up to eight waves a compute unit 8,192 of
+//     8 + 8 x 500 0.83 and 0.42, of 8 + 2 0.86 and 0.54; beyond, 40,000 x 200 of
+//     8 + 8 0.58 and 0.79, of 8 + 2 0.69 and 1.00, ledger backlog 32,768 of 8 + 8 x
+//     300 0.85 and 0.94, but of 5 + 5 0.86 and 0.82, least loaded 8 + 8 0.71 and 0.60;
+//   - nine to 32 a side, up to eight waves a compute unit: 2,047 of 2 + 32 x 400
+//     0.38 and 0.28; ledger backlog 4,000 of 16 + 16 x 500 0.49 and 0.39; the
+//     baselines and sampled candidates 2,000 of 32 + 32 x 800 0.68 and 0.42, but of
+//     24 + 3, in segments twice as wide as need be, 0.48 and 0.52.  Others with as
+//     many prefill instances: up to four (2,000 of 16 + 16 0.49 and 0.40; 4,000 of
+//     12 + 2 x 500 0.37 and 0.43), the widest up to two (1,000 of 32 + 32 x 800 0.55
+//     and 0.58).
+bool takes_lseg(const rt_point& p, double per_cu, bool many) {
+  const int P = p.n_prefill, D = p.n_decode, side = std::max(P, D);
+  const int mode = point_mode(p);
+  if (per_cu <= 2.0) return true;
+  const bool learned = mode == rt::kModeTrue || mode == rt::kModeProxy;
+  if (D == 1 && P >= 8) return per_cu <= 3.0;
+  if (side <= 4) return true;
+  const bool ledger = mode == rt::kModeProxy && P < 2 * D;
+  if (side <= 8) {
+    if (P >= D && per_cu > 8.0) return (ledger && P + D <= 12) || (!learned && P < 4 * D);
+    return !(learned && P + D <= 8 && per_cu > 12.0 && per_cu <= 16.0);
+  }
+  if (many || per_cu >= 8.0) return false;
+  if (P < D || ledger) return true;
+  const bool twice = P + D <= (side > 16 ? 32 : 16);  // as wide as need be
+  if (!learned && !(twice && P >= 8 * D)) return true;
+  return per_cu <= (P + D <= 48 ? 4.0 : 2.0);
+}
+
+// Plan.  Each point runs one kernel class: the one-wave class with its FIFOs in LDS
+// where that is the faster one (takes_lseg); otherwise the launch's size decides,
+// counted in waves of segments just wide enough for one instance per lane: with
+// fewer than two per SIMD every replica is a latency chain and takes the class
+// with the shortest step; with more, the GPU's issue rate is the limit and each
+// point takes the segment class with the fewest issue slots per replica-step
+// (lanes x step cost), of four lanes only where two waves per SIMD of those are
+// left (8,192 replicas of 2 + 12 x 300 with four lanes 0.40 ms, eight 0.25; 32,768
+// with four 0.79, eight 0.85, ledger backlog).
 //
 // Then replicas are grouped by class, longest first so that long chains start
 // early (equal lengths in replica order); empty replicas need no work.  Classes
@@ -262,19 +307,19 @@ void plan_launch(const rt_sim_points& sp, int64_t n, PlanBufs& b) {
     while (rt::sim_class(fit[j]).kind == rt::kLseg) ++j;
     return fit[j];
   };
-  double waves = 0.0, lds_waves = 0.0;
+  double waves = 0.0, lds_waves = 0.0, reps = 0.0;
   for (size_t k = 0; k < npts; ++k) {
     const int inst = sp.points[k].n_prefill + sp.points[k].n_decode;
     int S = rt::sim_class(other(k)).S;
     while (rt::sim_class(other(k)).kind == rt::kSeg && S / 2 >= inst) S /= 2;
     waves += (double)b.reps_of[k] * S / 64.0;
+    reps += (double)b.reps_of[k];
     lds_waves += (double)b.reps_of[k] * rt::sim_class(sp.classes[k][0]).S / 64.0;
   }
-  const bool many = waves >= 2.0 * kSimds, lds_many = many || lds_waves >= 2.0 * kSimds;
+  const bool many = waves >= 2.0 * kSimds, narrow = reps * 4.0 / 64.0 >= 2.0 * kSimds;
   for (size_t k = 0; k < npts; ++k) {
     const std::vector<int>& fit = sp.classes[k];
-    const bool small = std::max(sp.points[k].n_prefill, sp.points[k].n_decode) <= kSmallPool;
-    if (rt::sim_class(fit[0]).kind == rt::kLseg && (small || !lds_many)) {
+    if (rt::sim_class(fit[0]).kind == rt::kLseg && takes_lseg(sp.points[k], lds_waves / rt::kComputeUnits, many)) {
       b.choice[k] = fit[0];
       continue;
     }
@@ -283,7 +328,7 @@ void plan_launch(const rt_sim_points& sp, int64_t n, PlanBufs& b) {
     double best = -1.0;
     for (int c : fit) {
       const rt::SimClass sc = rt::sim_class(c);
-      if (sc.kind != rt::kSeg) continue;
+      if (sc.kind != rt::kSeg || (sc.S < 8 && !narrow)) continue;
       const double cost = sc.S * seg_step_cost(sc);
       if (best < 0.0 || cost < best) {
         best = cost;

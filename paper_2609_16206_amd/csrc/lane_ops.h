@@ -143,6 +143,25 @@ __device__ __forceinline__ int32_t wave_max_nonneg(int32_t v) {
   return (int32_t)u;
 }
 
+// Two broadcasts at once: x from the lane of each segment where `ox` holds and
+// y from the one where `oy` holds, the four halves reduced interleaved.
+template <int S>
+__device__ __forceinline__ void seg_bcast2_f64(double& x, bool ox, double& y, bool oy) {
+  uint32_t a = ox ? (uint32_t)__double2loint(x) : 0u, b = ox ? (uint32_t)__double2hiint(x) : 0u;
+  uint32_t c = oy ? (uint32_t)__double2loint(y) : 0u, d = oy ? (uint32_t)__double2hiint(y) : 0u;
+  if constexpr (S >= 2) { a |= dpp<0xB1>(a); b |= dpp<0xB1>(b); c |= dpp<0xB1>(c); d |= dpp<0xB1>(d); }
+  if constexpr (S >= 4) { a |= dpp<0x4E>(a); b |= dpp<0x4E>(b); c |= dpp<0x4E>(c); d |= dpp<0x4E>(d); }
+  if constexpr (S >= 8) { a |= dpp<0x141>(a); b |= dpp<0x141>(b); c |= dpp<0x141>(c); d |= dpp<0x141>(d); }
+  if constexpr (S >= 16) { a |= dpp<0x140>(a); b |= dpp<0x140>(b); c |= dpp<0x140>(c); d |= dpp<0x140>(d); }
+  const auto orf = [](uint32_t x, uint32_t y) { return x | y; };
+  a = cross_rows<S>(a, orf);
+  b = cross_rows<S>(b, orf);
+  c = cross_rows<S>(c, orf);
+  d = cross_rows<S>(d, orf);
+  x = __hiloint2double((int)b, (int)a);
+  y = __hiloint2double((int)d, (int)c);
+}
+
 // Values of two lanes of each segment, read by every lane of it: x from
 // segment lane lx and y from segment lane ly (each in [0, S)), one
 // ds_bpermute per 32-bit half (no memory access: the lanes exchange through

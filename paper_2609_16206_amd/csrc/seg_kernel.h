@@ -491,13 +491,22 @@ __global__ void __launch_bounds__(64 * kWaves) seg_kernel(SimArgs a) {
     const int32_t wp = seg_first<S>(kp0 == kp, lane);  // winning lanes
     const int32_t wd = seg_first<S>(kd0 == kd, lane);
     // the winning slots and the winners' busy-until, read by every lane of
-    // the segment through lane permutes (so that every lane forms both ends)
+    // the segment (so that every lane forms both ends): from 8 lanes up
+    // through lane permutes, below that through DPP reductions
     int32_t mp = 0, md = 0;
     double busy_p = bbusy, busy_d = bbusy;
-    seg_pick2_f64<S>(busy_p, wp, busy_d, wd, lane);
-    if constexpr (M > 1) {
-      mp = seg_pick<S>(bm, wp, lane);
-      md = seg_pick<S>(bm, wd, lane);
+    if constexpr (S >= 8) {
+      seg_pick2_f64<S>(busy_p, wp, busy_d, wd, lane);
+      if constexpr (M > 1) {
+        mp = seg_pick<S>(bm, wp, lane);
+        md = seg_pick<S>(bm, wd, lane);
+      }
+    } else {
+      if constexpr (M > 1) {
+        mp = (int32_t)seg_or<S>(sl == wp ? (uint32_t)bm : 0u);
+        md = (int32_t)seg_or<S>(sl == wd ? (uint32_t)bm : 0u);
+      }
+      seg_bcast2_f64<S>(busy_p, sl == wp, busy_d, sl == wd);
     }
     const int32_t ip = wp * M + mp;
     const int32_t id = (wd - LP) * M + md;
@@ -644,14 +653,13 @@ hipError_t launch_seg(const SimArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The segment widths and lane depths compiled for every mode.  (Pools of at
-// most eight instances a side run the kernel of lseg_kernel.h, so narrower
-// segments of one instance per lane hold nothing that is left, and of the
-// deeper ones those of 2 and 4 lanes were slower than the next wider: a wave of
-// 16 or 32 replicas takes the slow path on almost every step.)
-#define RT_SEG_FOR_EACH(X)                                              \
-  X(16, 1) X(32, 1) X(64, 1) X(8, 2) X(16, 2) X(32, 2) X(64, 2) X(8, 3) \
-  X(16, 3) X(32, 3) X(64, 3) X(8, 4) X(16, 4) X(32, 4) X(64, 4)
+// The segment widths and lane depths compiled for every mode.  (Narrower segments
+// of one instance per lane hold nothing that is left: pools of at most four
+// instances a side run the kernel of lseg_kernel.h, but for one shape.)
+#define RT_SEG_FOR_EACH(X)                                                      \
+  X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(8, 2) X(16, 2) X(32, 2) X(64, 2) \
+  X(4, 3) X(8, 3) X(16, 3) X(32, 3) X(64, 3) X(4, 4) X(8, 4) X(16, 4) X(32, 4)  \
+  X(64, 4)
 
 // Launch the (S, M) kernel of one mode (defined in one source file per mode).
 template <int kMode>
