@@ -1002,9 +1002,11 @@ hipError_t launch_bat(const SimClass& c, const SimArgs& a, const BatScratch& b, 
 }
 
 // Scratch owners of a launch of class c over n_work replicas: the lanes of a
-// segment class, the replicas of the others.
+// segment class, in whole workgroups, the replicas of the others (one a
+// workgroup: no more than there are, each is a pool's worth of rings).
 int64_t bat_lanes(const SimClass& c, int64_t n_work) {
-  const int64_t lanes = n_work * (int64_t)(c.S > 64 ? 1 : c.S);
+  if (c.S > 64) return n_work;
+  const int64_t lanes = n_work * (int64_t)c.S;
   return (lanes + bat::kBlock - 1) / bat::kBlock * bat::kBlock;
 }
 

@@ -5,7 +5,9 @@ departures at once than a wave lists, a full ring; and the pools that still
 take the general kernel."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2609_16206_amd import rt_router as R
 from paper_2609_16206_amd import workload as W
 from tests.gpu_common import log, run_sim
 from tests.parity import check_properties, follow_replicas, goodput_recount
@@ -75,3 +77,23 @@ def test_full_ring_stops_the_replica():
     tr["arrival_ns"][:300] //= 64
     _, _, _, flags = run_sim(pts, tr)
     assert flags == 8
+
+
+def test_scratch_is_one_pool_of_rings_a_replica():
+    """32 bytes a ring place, P + D instances a replica: 604 MB for one replica of 32 + 256 with the largest batch_cap,
+    and no more than that is taken."""
+    pt = dict(W.make_point(32, 256, n_classes=3, service="batched"), batch_cap=65536)
+    tr = _trace([pt], [300], 2.0)
+    sim = R.Simulator([pt])
+    dtr = R.to_device(tr)
+    out = R.alloc_outputs(300)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    sim.run(dtr, out)
+    torch.cuda.synchronize()
+    taken = before - torch.cuda.mem_get_info()[0]
+    flags = sim.data_status()
+    sim.close()
+    assert flags == 0 and taken <= 288 * 65536 * 32 + (64 << 20), taken
+    gpu = {k: v.cpu().numpy() for k, v in out.items()}
+    follow_replicas([pt], tr, gpu, [0])
