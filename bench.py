@@ -41,10 +41,15 @@ SCORE_OPS_PER_PAIR = 10
 SCORE_OPS_PER_REQ = 0
 # The design notes' own recount of the written arithmetic (reported beside
 # the fraction above, labelled): backlog 4, press 3, factor 2, size 2, load 2,
-# queue 2, sums 2, argmin 1, release 1 = 19 per pair and 25 per request; the
-# scorer 14 per pair and 4 per request.
+# queue 2, sums 2, argmin 1, release 1 = 19 per pair and 25 per request.  The
+# scorer forms backlog and queue terms once per instance and takes its argmin
+# four pairs at a time: occupancy + need, its share of the capacity, factor (rho
+# is 1), size 2, load, sums 2 and a quarter of five = 9.25 per pair; about 50 per
+# request, 32 of them for the winning four taken again.  Rows form theirs per
+# pair: 14 and 4.
 RECOUNT_SIM = (19, 25)
-RECOUNT_SCORE = (14, 4)
+RECOUNT_SCORE = (9.25, 50)
+RECOUNT_SCORE_ROWS = (14, 4)
 SCORE_BYTES_PER_REQ = 4 + 4 + 1 + 4 + 4  # p, o^, class in; index, score out
 SCORE_BYTES_PER_PAIR_ROWS = 4 + 4 + 4  # per-request snapshot rows: backlog, queue, occupancy
 
@@ -82,7 +87,7 @@ SIM_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in (
     "seg_kernel.h", "lseg_kernel.h", "wseg_kernel.h", "seg_true.hip", "seg_proxy.hip", "seg_base.hip", "seg_true_s.hip", "seg_proxy_s.hip", "seg_classes.hip",
     "lane_ops.h", "rt_internal.h", "api.hip")]
 BAT_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in ("bat_kernel.hip", "lbat_kernel.h", "lane_ops.h", "rt_internal.h", "api.hip", "seg_classes.hip")]
-SCORE_SOURCES = ["paper_2609_16206_amd/csrc/score_kernel.hip", "paper_2609_16206_amd/csrc/rt_internal.h"]
+SCORE_SOURCES = ["paper_2609_16206_amd/csrc/" + f for f in ("score_kernel.hip", "lane_ops.h", "rt_internal.h")]
 
 
 def _traffic(kernel_tag, workload_name, sources):
@@ -286,7 +291,8 @@ def bench_scorer(args, rows=False):
         roof["per_unit"] = (f"{SCORE_OPS_PER_PAIR} lane-ops/pair (recount {RECOUNT_SCORE[0]}/pair + "
                             f"{RECOUNT_SCORE[1]}/request)")
     roof["frac"] = roof["achieved"] / roof["peak"]
-    roof["frac_alu_recount"] = (pairs * RECOUNT_SCORE[0] + n_req * RECOUNT_SCORE[1]) / kernel_s / ALU_PEAK
+    recount = RECOUNT_SCORE_ROWS if rows else RECOUNT_SCORE
+    roof["frac_alu_recount"] = (pairs * recount[0] + n_req * recount[1]) / kernel_s / ALU_PEAK
     roof["kernel_ms"] = kernel_s * 1e3
     wname = f"scorer-{n_req}x{n_inst}-" + ("per-request" if rows else "shared")
     res = dict(metric=METRIC, value=n_req * args.steps / dt, unit="requests/s", n_gpus=1, steps=args.steps,

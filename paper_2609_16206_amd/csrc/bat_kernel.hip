@@ -505,9 +505,10 @@ struct Req {
   uint4 ws;
 };
 
-// One instance of the wide kernel, in registers (a lane holds M): the
-// batch's state, the first two entries of its rings with the front
-// requests' data, and the rings' cached tails.
+// One instance of the wide kernel (a lane holds M): the batch's state, the first
+// two entries of its rings with the front requests' data, and the rings' cached
+// tails, some 50 registers.  In registers with M = 1; with M = 2 and 3 (pools of
+// about 500 to 1,500 instances) parts of it spill, 360 and 930 bytes a lane.
 struct BInst {
   double v, tl, left, kv, pend, owed;
   int32_t q, nact, head, nw, wh;
@@ -557,7 +558,7 @@ __device__ __forceinline__ void init_binst(BInst& x) {
 // What bounds it: a step's chain of events and its two barriers.  64 replicas
 // of 32 + 256 instances x 400 requests: 92 ms with one replica per lane
 // (bat_kernel, which walks the 288 instances one after the other in scratch),
-// 1.10 ms so; 256 of 128 + 1,024 x 60: 80 and 1.6 ms; 32,768 of 1 + 130 x 40,
+// 1.06 ms so; 256 of 128 + 1,024 x 60: 80 and 1.6 ms; 32,768 of 1 + 130 x 40,
 // enough for every lane of bat_kernel: 9.7 and 7.2 ms.
 // Departures a wave lists before they are taken.  One round adds at most one
 // per prefill instance of the wave, which is no more (so a list that is taken

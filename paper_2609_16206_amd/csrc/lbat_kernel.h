@@ -749,7 +749,7 @@ hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t st
 // replicas, so more slots a wave, and their rings would be too short for the
 // batches of small pools: 65,536 of 1 + 2 x 1,000 8.4 ms with two waves and 17.7
 // with three, of 2 + 6 13.1 and 20.9.  With three, segments of 32 lanes spill 36
-// registers a lane and those of 64 two (the figures have that in them); two
+// registers a lane and those of 64 four (the figures have that in them); two
 // instances per lane fill the registers of two waves.
 template <int S, int M>
 hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream) {

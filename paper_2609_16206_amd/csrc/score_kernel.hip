@@ -63,9 +63,10 @@ __device__ __forceinline__ void score_loop(const SnapEntry* snap, int n, const S
 // float minima order as the keys do.  Costs are taken four at a time: their
 // minimum (two instructions), one compare and two selects per four instead of
 // per one; the index within the winning four is found afterwards by taking
-// its costs again.  9.3 VALU instructions a pair (8.3 with rho 1, whose
-// product changes nothing) against 17 above; 2^20 requests x 64 instances:
-// 25.9 us with the loop above, 16.8 us so.
+// its costs again.  10.4 VALU instructions a pair (9.4 with rho 1, whose product
+// changes nothing: four products, four sums, a quarter of five for the minimum and
+// the loop's own) against 17 above; 2^20 requests x 64 instances: 25.9 us with the
+// loop above, 16.8 us so.
 template <bool kRho1>
 __device__ __forceinline__ float plain_cost(const SnapEntry& e, const ScoreArgs& a, float sg, float work, float need) {
   const float press = (e.kvf + need) * a.inv_cap;
@@ -197,7 +198,7 @@ __global__ void __launch_bounds__(kBlock) score_shared_kernel(ScoreArgs a) {
 // and the lowest index that holds it.  Stride 0 (one snapshot for every
 // request) is a row like any other.  Against one 64-lane segment, one load
 // per array in flight and a 64-bit shuffle reduction per request: 300,007 rows
-// of 37 instances 87.7 -> 28.9 us; 48 requests x 1,000 shared instances
+// of 37 instances 87.7 -> 30.6 us; 48 requests x 1,000 shared instances
 // 90 us with a thread per request, 10 us (the launch itself) so.
 template <int L, int U, int G>
 __global__ void __launch_bounds__(kBlock) score_rows_kernel(ScoreArgs a) {
