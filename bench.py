@@ -42,13 +42,14 @@ SCORE_OPS_PER_REQ = 0
 # The design notes' own recount of the written arithmetic (reported beside
 # the fraction above, labelled): backlog 4, press 3, factor 2, size 2, load 2,
 # queue 2, sums 2, argmin 1, release 1 = 19 per pair and 25 per request.  The
-# scorer forms backlog and queue terms once per instance and takes its argmin
-# four pairs at a time: occupancy + need, its share of the capacity, factor (rho
-# is 1), size 2, load, sums 2 and a quarter of five = 9.25 per pair; about 50 per
-# request, 32 of them for the winning four taken again.  Rows form theirs per
-# pair: 14 and 4.
+# shared scorer forms backlog and queue terms once per instance and takes its
+# argmin four pairs at a time: occupancy + need, its share of the capacity,
+# factor (rho is 1), size 2, load, sums 2, half a minimum and a quarter of a
+# compare = 8.75 per pair, and about 45 per request (the winning four again).
+# That is less than the count above, so its fraction by that can pass 1.  Rows
+# form theirs per pair: 14 and 4.
 RECOUNT_SIM = (19, 25)
-RECOUNT_SCORE = (9.25, 50)
+RECOUNT_SCORE = (8.75, 45)
 RECOUNT_SCORE_ROWS = (14, 4)
 SCORE_BYTES_PER_REQ = 4 + 4 + 1 + 4 + 4  # p, o^, class in; index, score out
 SCORE_BYTES_PER_PAIR_ROWS = 4 + 4 + 4  # per-request snapshot rows: backlog, queue, occupancy
