@@ -73,8 +73,7 @@ def test_mixed_shapes_betas_and_serial_points():
     1: pure processor sharing) next to serial points in one call, so both
     kernel kinds run side by side; ragged and empty replicas."""
     # segment widths 4, 8, 16, 32 and 64 (P + D = 64 exactly), two instances
-    # per lane up to 128 instances, and beyond that the one-replica-per-lane
-    # kernel
+    # per lane up to 128 instances, and beyond that one replica per workgroup
     shapes = [(1, 1), (2, 6), (3, 9), (5, 16), (8, 8), (33, 64), (2, 2), (4, 12), (32, 32), (20, 44), (40, 100)]
     betas = [(0.0, 0.0), (W.BATCH_BETA, W.BATCH_BETA), (1.0, 0.25), (0.5, 1.0)]
     pts = []

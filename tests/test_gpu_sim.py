@@ -271,14 +271,17 @@ def test_coarse_grid_ties_many_small_replicas():
     log(f"serial coarse grid: {rep}")
 
 
+# In turn: segments of 8 lanes (four, two and one wave per SIMD), of 16, of 32 and of 64, queues in LDS; then queues in
+# HBM, one instance per lane in segments of 8, 16, 32 and 64 lanes, and several in segments of 4.
 @pytest.mark.parametrize("P,D,n_rep", [(1, 1, 32768), (1, 2, 16384), (1, 1, 8192), (2, 6, 4096), (8, 8, 2048),
-                                       (16, 16, 1024)])
+                                       (16, 16, 1024), (5, 3, 8900), (9, 7, 4200), (17, 15, 1100), (33, 20, 600),
+                                       (8, 2, 33000)])
 def test_outcome_blocks_every_residue(P, D, n_rep):
     """The one-wave kernels write outcomes in blocks of S steps (lane k of a
-    segment keeps step block start + k).  Replica lengths cycle through
-    1..130, so a replica's last block ends at every residue modulo the
-    segment width; the replica counts are chosen so that the planner's
-    widening stops at S = 2, 4, 8, 16, 32 and 64 in turn (one wave per SIMD)."""
+    segment keeps step block start + k) or of S / 2 (queues in LDS).  Replica
+    lengths cycle through 1..130, so a replica's last block ends at every
+    residue modulo the segment width; the replica counts are chosen so that the
+    planner stops at the widths above."""
     pts = [W.make_point(P, D, n_classes=3, kv_cap=50_000)]
     lengths = [1 + (i % 130) for i in range(n_rep)]
     tr = _ragged_trace(pts, lengths, seed=23, rate_scale=1.2)
