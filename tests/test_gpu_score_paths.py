@@ -23,6 +23,8 @@ def _spoil(kind, d, prm):
             d[k][:] = d[k][0]
     elif kind == "occupancy 2^24":
         d["kv_occ"][w // 2] = (1 << 24) - 300  # + need: above 2^24 for most requests
+    elif kind == "occupancy 2^31":
+        d["kv_occ"][::2] = (1 << 31) - 1  # + need: above 2^31
     elif kind == "negative occupancy":
         d["kv_occ"][w - 1] = -70_000
     elif kind == "infinite cost":
@@ -32,8 +34,8 @@ def _spoil(kind, d, prm):
         prm.update(w_s=3e38, rho=3e38, sigma=[0.0, 2.0] + [1.0] * 6)  # inf * 0
 
 
-@pytest.mark.parametrize("kind", ["plain", "rho 2.5", "zero weights", "equal", "occupancy 2^24", "negative occupancy",
-                                  "infinite cost", "nan cost"])
+@pytest.mark.parametrize("kind", ["plain", "rho 2.5", "zero weights", "equal", "occupancy 2^24", "occupancy 2^31",
+                                  "negative occupancy", "infinite cost", "nan cost"])
 @pytest.mark.parametrize("n_inst", [1, 3, 4, 5, 64, 67])
 def test_shared_snapshot_loops(n_inst, kind):
     d = W.scorer_inputs(n_req=(1 << 16) + 3, n_inst=n_inst, seed=20 + n_inst)
