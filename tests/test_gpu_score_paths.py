@@ -56,7 +56,7 @@ def test_shared_snapshot_loops(n_inst, kind):
 
 
 @pytest.mark.parametrize("shared", [False, True])
-@pytest.mark.parametrize("n_inst,stride", [(2, 2), (5, 7), (15, 15), (16, 17), (17, 17), (33, 35), (48, 49), (63, 63),
+@pytest.mark.parametrize("n_inst,stride", [(1, 1), (1, 3), (2, 2), (2, 5), (3, 3), (5, 7), (15, 15), (16, 17), (17, 17), (33, 35), (48, 49), (63, 63),
                                            (64, 65), (127, 127), (128, 131), (193, 193), (257, 259)])
 def test_lanes_per_request(n_inst, stride, shared):
     n_req = 1031
