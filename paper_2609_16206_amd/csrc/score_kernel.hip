@@ -173,17 +173,19 @@ __global__ void __launch_bounds__(kBlock) score_shared_kernel(ScoreArgs a) {
         need[r] = a.pool == 1 ? (int64_t)p + oh : (int64_t)p;
       }
     }
-    // The plain loop's conditions.  The snapshot's terms are finite and not
-    // negative; occupancy + need stays below 2^24 for the largest occupancy (a
-    // negative one counts as one of 2^31 or more);
-    // and work * (1 + rho * press) is finite for it, so for every one (each
+    // The plain loop's conditions (from ten instances on: taking the winning four
+    // again costs what the loop saves on fewer; 4,000,000 requests x 5 23.8 us and
+    // 21.0 with the other loop, x 10 26.0 and 25.9, x 12 26.0 and 28.3).  The
+    // snapshot's terms are finite and not negative; occupancy + need stays below
+    // 2^24 for the largest occupancy (a negative one counts as one of 2^31 or
+    // more); and work * (1 + rho * press) is finite for it, so for every one (each
     // operation is monotone).  Then every product and sum of a cost is +0,
     // positive or +inf (weights are +0 or positive), and +inf meets neither
     // 0 * inf nor inf - inf: sigma and the reciprocal capacity are finite.
     const float top = work[r] * (1.0f + a.rho * ((float)((int64_t)kvm + need[r]) * a.inv_cap));
     plain &= (int64_t)kvm + need[r] < (1 << 24) && top < __builtin_huge_valf();
   }
-  if (__all(plain)) {
+  if (n >= 10 && __all(plain)) {
     if (a.rho == 1.0f)
       plain_loop<true>(snap, n, a, sg, work, need, bkey, bi);
     else

@@ -36,7 +36,7 @@ def _spoil(kind, d, prm):
 
 @pytest.mark.parametrize("kind", ["plain", "rho 2.5", "zero weights", "equal", "occupancy 2^24", "occupancy 2^31",
                                   "negative occupancy", "infinite cost", "nan cost"])
-@pytest.mark.parametrize("n_inst", [1, 3, 4, 5, 64, 67])
+@pytest.mark.parametrize("n_inst", [1, 3, 4, 5, 9, 10, 11, 12, 13, 64, 67])
 def test_shared_snapshot_loops(n_inst, kind):
     d = W.scorer_inputs(n_req=(1 << 16) + 3, n_inst=n_inst, seed=20 + n_inst)
     prm = W.scorer_params()
