@@ -744,8 +744,9 @@ hipError_t launch_lbat_occ(const SimArgs& a, const BatScratch& b, hipStream_t st
 
 // Three waves per SIMD where a call has more than two, two otherwise.  Segments
 // of 32 and 64 lanes gain from the third (with rings of at least two and one
-// entries): 16,384 replicas of 3 + 14 x 500 4.62 and 3.84 ms, 5,120 x 400 1.54
-// and 1.16, 2,560 of 10 + 29 x 300 0.98 and 0.75.  Narrower ones have more
+// entries, one and one where all waves then fit in one pass): 16,384 replicas of
+// 3 + 14 x 500 4.62 and 3.84 ms, 5,120 x 400 1.54 and 1.16, 2,560 of 10 + 29 x 300
+// 0.98 and 0.75, 2,300 of 2 + 62 x 150 0.49 and 0.37.  Narrower ones have more
 // replicas, so more slots a wave, and their rings would be too short for the
 // batches of small pools: 65,536 of 1 + 2 x 1,000 8.4 ms with two waves and 17.7
 // with three, of 2 + 6 13.1 and 20.9.  With three, segments of 32 lanes spill 36
@@ -755,8 +756,10 @@ template <int S, int M>
 hipError_t launch_lbat(const SimArgs& a, const BatScratch& b, hipStream_t stream) {
   if constexpr (M == 1 && S >= 32) {
     using Dm = LbatDims<S>;
-    const uint32_t bytes = (uint32_t)Dm::kSegs * (uint32_t)a.max_inst * 32 * (2 + 1 + 1) + Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0);
-    if (waves_per_cu(a.call_waves) > 8 && bytes <= lds_share(a.call_waves, 12).bytes)
+    const int64_t per_cu = waves_per_cu(a.call_waves);
+    const uint32_t slots = (uint32_t)Dm::kSegs * (uint32_t)a.max_inst, places = per_cu <= 12 ? 1 + 1 + 1 : 2 + 1 + 1;
+    const uint32_t bytes = slots * 32 * places + Dm::kCand0 + (a.samp ? Dm::kCandBytes : 0);
+    if (per_cu > 8 && bytes <= lds_share(a.call_waves, 12).bytes)
       return launch_lbat_occ<S, M, 3>(a, b, stream);
   }
   return launch_lbat_occ<S, M, 2>(a, b, stream);

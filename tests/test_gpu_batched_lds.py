@@ -148,11 +148,15 @@ def test_rejections_around_a_full_queue(width, where, late):
 
 # 5 to 7 and 9 to 11 waves a compute unit (and a ragged last workgroup).
 @pytest.mark.parametrize("P,D,n", [(2, 6, 4610), (2, 6, 8300), (1, 2, 17100), (3, 14, 2500), (3, 14, 4200), (12, 20, 4600),
-                                   (10, 29, 1300), (10, 29, 2070), (8, 64, 1100)])
+                                   (10, 29, 1300), (10, 29, 2070), (1, 31, 4300), (2, 62, 2300), (32, 32, 3080),
+                                   (8, 64, 1100)])
 def test_waves_between_whole_workgroups(P, D, n):
-    pts = _points(P, D)
-    tr = _bursts(pts, [20 - (i % 5) for i in range(n)], 10, 10**9)
-    gpu, g, met, flags = run_sim(pts, tr)
-    assert flags == 0
-    check_properties(pts, tr, gpu)
-    follow_replicas(pts, tr, gpu, range(0, n, n // 60), gpu_goodput=g, gpu_met=met)
+    # with and without candidate words, which take room from the rings
+    for pts in (_points(P, D), _points(P, D)[:4]):
+        tr = _bursts(pts, [20 - (i % 5) for i in range(n)], 10, 10**9)
+        if len(pts) == 4:
+            del tr["sample_bits"]
+        gpu, g, met, flags = run_sim(pts, tr)
+        assert flags == 0
+        check_properties(pts, tr, gpu)
+        follow_replicas(pts, tr, gpu, range(0, n, n // 60), gpu_goodput=g, gpu_met=met)
